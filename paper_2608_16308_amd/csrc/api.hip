@@ -47,17 +47,23 @@ dbs_status check_device()
 // pad: zeroed bytes after the data (the payload gets 16, so that a 16-byte
 // load of the chunk holding a record's last byte stays inside the allocation)
 template <class T>
-dbs_status dev_upload(std::vector<void *> &allocs, const std::vector<T> &h, const T **out, size_t pad = 0)
+dbs_status dev_upload(std::vector<void *> &allocs, const T *h, size_t count, const T **out, size_t pad = 0)
 {
-    const size_t data = h.size() * sizeof(T);
+    const size_t data = count * sizeof(T);
     size_t bytes = std::max<size_t>(data + pad, 16);
     void *p = nullptr;
     HIP_TRY(hipMalloc(&p, bytes), "hipMalloc (matrix)");
     allocs.push_back(p);
     if (bytes > data) HIP_TRY(hipMemset((char *)p + data, 0, bytes - data), "hipMemset (matrix)");
-    if (!h.empty()) HIP_TRY(hipMemcpy(p, h.data(), data, hipMemcpyHostToDevice), "hipMemcpy (matrix)");
+    if (data) HIP_TRY(hipMemcpy(p, h, data, hipMemcpyHostToDevice), "hipMemcpy (matrix)");
     *out = (const T *)p;
     return DBS_OK;
+}
+
+template <class T>
+dbs_status dev_upload(std::vector<void *> &allocs, const std::vector<T> &h, const T **out, size_t pad = 0)
+{
+    return dev_upload(allocs, h.data(), h.size(), out, pad);
 }
 
 template <class T>
@@ -177,6 +183,50 @@ dbs_status check_ctx(dbs_ctx *ctx, const dbs_matrix *A)
 // ---------------------------------------------------------------------------
 // matrix
 // ---------------------------------------------------------------------------
+// The column-entry view of a matrix that has its row-entry view.
+static dbs_status column_entries(dbs_matrix *A)
+{
+    DevMatrix &d = A->d;
+    const int32_t vb = (int32_t)dtype_bytes((dbs_dtype)d.dtype);
+    int32_t *ptr = nullptr, *next = nullptr, *row = nullptr;
+    void *val = nullptr;
+    std::vector<int32_t> h;
+    try {
+        h.resize((size_t)d.n + 1);
+    } catch (const std::bad_alloc &) {
+        return dbs_fail(DBS_ERR_ALLOC, "host allocation failed during upload");
+    }
+    auto alloc = [&](void **p, size_t bytes) -> hipError_t {
+        const hipError_t e = hipMalloc(p, std::max<size_t>(bytes, 16));
+        if (e == hipSuccess) A->allocs.push_back(*p);
+        return e;
+    };
+    const size_t np = ((size_t)d.n + 1) * 4;
+    HIP_TRY(alloc((void **)&ptr, np), "hipMalloc (column entries)");
+    HIP_TRY(alloc((void **)&row, (size_t)d.re_nnz * 4), "hipMalloc (column entries)");
+    if (vb) HIP_TRY(alloc(&val, (size_t)d.re_nnz * vb), "hipMalloc (column entries)");
+    HIP_TRY(hipMalloc((void **)&next, np), "hipMalloc (column entries)");
+    auto build = [&]() -> hipError_t {
+        hipError_t e = hipMemset(next, 0, np);
+        if (e == hipSuccess) e = launch_ce_count(d, next, nullptr);
+        if (e == hipSuccess) e = hipMemcpy(h.data() + 1, next, np - 4, hipMemcpyDeviceToHost);
+        if (e != hipSuccess) return e;
+        h[0] = 0;
+        for (int32_t j = 0; j < d.n; ++j) h[(size_t)j + 1] += h[(size_t)j];
+        e = hipMemcpy(ptr, h.data(), np, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(next, h.data(), np, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = launch_ce_fill(d, vb, next, row, val, nullptr);
+        return e == hipSuccess ? hipStreamSynchronize(nullptr) : e;
+    };
+    const hipError_t e = build();
+    (void)hipFree(next);
+    HIP_TRY(e, "column entries");
+    d.ce_ptr = ptr;
+    d.ce_row = row;
+    d.ce_val = val;
+    return DBS_OK;
+}
+
 extern "C" dbs_status dbs_matrix_upload(const dbs_host_matrix *h, dbs_matrix **out)
 {
     if (!h || !out) return dbs_fail(DBS_ERR_ARG, "dbs_matrix_upload: NULL argument");
@@ -275,6 +325,26 @@ extern "C" dbs_status dbs_matrix_upload(const dbs_host_matrix *h, dbs_matrix **o
         free_all(A->allocs);
         delete A;
         return s2;
+    }
+    if (h->nre_chunk > 0) {
+        const size_t ncol = (size_t)h->nre_chunk * RE_CHUNK, vbytes = (size_t)h->nnz * dtype_bytes(h->dtype);
+        const uint8_t *rv = nullptr;
+        if ((s2 = dev_upload(A->allocs, h->re_col.get(), ncol, &d.re_col)) != DBS_OK ||
+            (s2 = dev_upload(A->allocs, h->re_val.get(), vbytes, &rv)) != DBS_OK ||
+            (s2 = dev_upload(A->allocs, h->re_row, &d.re_row)) != DBS_OK ||
+            (s2 = dev_upload(A->allocs, h->re_chord, &d.re_chord)) != DBS_OK) {
+            free_all(A->allocs);
+            delete A;
+            return s2;
+        }
+        d.re_val = rv;
+        d.re_nnz = (int32_t)h->nnz;
+        d.re_nchunk = (int32_t)h->nre_chunk;
+        if ((s2 = column_entries(A)) != DBS_OK) {
+            free_all(A->allocs);
+            delete A;
+            return s2;
+        }
     }
     d.nheavy = (int64_t)hv_col.size();
     d.nchunk = (int64_t)hv_crow.size();
@@ -513,7 +583,7 @@ template <class Run>
 dbs_status spmspv_launches(const dbs_matrix *A, DevCtx &c, hipStream_t s, int mode, dbs_semiring sr,
                            int32_t x_nnz, const int32_t *d_x_idx, const void *d_x_val, const uint32_t *d_mask,
                            int complement_mask, dbs_path path, float th3, int32_t *d_y_idx, void *d_y_val,
-                           int32_t *d_y_nnz, bool single, Run &&run)
+                           int32_t *d_y_nnz, bool single, bool stats, Run &&run)
 {
     if (single && fused_fits(A->d, x_nnz)) {
         // a short index list: the whole call in one launch (the device
@@ -541,28 +611,59 @@ dbs_status spmspv_launches(const dbs_matrix *A, DevCtx &c, hipStream_t s, int mo
         // the smallest N_nzblk the paper's rule leaves to pull
         const int64_t a = std::max<int64_t>(nlo, (int64_t)std::ceil(lim));
         if ((double)x_nnz < lim) launch_path = DBS_PATH_PUSH;
-        else if ((double)nlo >= lim_any) launch_path = DBS_PATH_PULL;
+        // (also when x has too many indices to be spread below lim_s)
+        else if ((double)nlo >= lim_any || ((double)nlo >= lim && (double)x_nnz >= 2.0 * lim_s))
+            launch_path = DBS_PATH_PULL;
         else if ((double)nhi < lim_s && 2 * a > x_nnz) launch_path = DBS_PATH_PUSH;  // spread for every such N
     }
     dbs_status st;
-    if (small_x_fits(A->d, (int32_t)x_nnz)) {
-        // a short index list: blocker and scan in one workgroup
-        st = run(DBS_K_SCAN, [&] {
-            return launch_small_x(A->d, c, mode, (int32_t)x_nnz, d_x_idx, d_x_val, launch_path,
-                                  (double)norm_th3(th3), spread_th3(th3), s);
+    const int cm = complement_mask ? 1 : 0;
+    const double t3 = (double)norm_th3(th3), t3s = spread_th3(th3);
+    // A matrix of short COO blocks is traversed over its entry views: pull
+    // streams the row-entry view, push walks the listed columns (their items
+    // fit the item list up to one index per vector block; an automatic choice
+    // of push with the default th3 has at most a quarter of that).  No scan
+    // runs; only a call that asks for statistics lets one count afterwards.
+    const bool entries = A->d.re_nchunk > 0;
+    const bool items = entries && launch_path != DBS_PATH_PULL && x_nnz <= A->d.nbc;
+    if (items || (entries && launch_path == DBS_PATH_PULL)) {
+        st = run(DBS_K_SCATTER, [&] {
+            return items ? launch_entry_scatter(A->d, c, mode, x_nnz, d_x_idx, d_x_val, s)
+                         : launch_scatter(A->d, c, mode, x_nnz, d_x_idx, d_x_val, s);
         });
         if (st != DBS_OK) return st;
-    } else {
-        st = run(DBS_K_SCATTER, [&] { return launch_scatter(A->d, c, mode, x_nnz, d_x_idx, d_x_val, s); });
+        st = run(DBS_K_MAIN, [&] {
+            return launch_path == DBS_PATH_PULL   ? launch_entry_pull(A->d, c, mode, d_mask, cm, false, s)
+                   : launch_path == DBS_PATH_PUSH ? launch_entry_push(A->d, c, mode, d_mask, cm, s)
+                                                  : launch_entry_auto(A->d, c, mode, d_mask, cm, t3, t3s, s);
+        });
         if (st != DBS_OK) return st;
-        st = run(DBS_K_SCAN,
-                 [&] { return launch_scan(A->d, c, launch_path, (double)norm_th3(th3), spread_th3(th3), s); });
+        if (stats) {
+            st = run(DBS_K_SCAN, [&] { return launch_scan(A->d, c, launch_path, t3, t3s, s); });
+            if (st != DBS_OK) return st;
+        }
+    } else {
+        if (small_x_fits(A->d, (int32_t)x_nnz)) {
+            // a short index list: blocker and scan in one workgroup
+            st = run(DBS_K_SCAN, [&] {
+                return launch_small_x(A->d, c, mode, (int32_t)x_nnz, d_x_idx, d_x_val, launch_path, t3, t3s, s);
+            });
+            if (st != DBS_OK) return st;
+        } else {
+            st = run(DBS_K_SCATTER, [&] { return launch_scatter(A->d, c, mode, x_nnz, d_x_idx, d_x_val, s); });
+            if (st != DBS_OK) return st;
+            st = run(DBS_K_SCAN, [&] { return launch_scan(A->d, c, launch_path, t3, t3s, s); });
+            if (st != DBS_OK) return st;
+        }
+        if (entries && launch_path == DBS_PATH_AUTO) {
+            st = run(DBS_K_MAIN, [&] { return launch_entry_pull(A->d, c, mode, d_mask, cm, true, s); });
+            if (st != DBS_OK) return st;
+            launch_path = DBS_PATH_PUSH;  // (the push kernel, if the device chose it)
+        }
+        st = run(DBS_K_MAIN,
+                 [&] { return launch_main(A->d, c, mode, c.xd, d_mask, cm, nullptr, launch_path, s); });
         if (st != DBS_OK) return st;
     }
-    st = run(DBS_K_MAIN, [&] {
-        return launch_main(A->d, c, mode, c.xd, d_mask, complement_mask ? 1 : 0, nullptr, launch_path, s);
-    });
-    if (st != DBS_OK) return st;
     return run(DBS_K_FINALIZE, [&] {
         return launch_finalize(A->d, c, mode, d_y_idx, sr == DBS_OR_AND ? nullptr : d_y_val, d_y_nnz, d_x_idx,
                                x_nnz, s);
@@ -582,7 +683,7 @@ extern "C" dbs_status dbs_spmspv(dbs_ctx *ctx, const dbs_matrix *A, dbs_semiring
     st = spmspv_check_args(A, sr, x_nnz, d_x_idx, d_x_val, path, d_y_idx, d_y_val, d_y_nnz, &mode);
     if (st != DBS_OK) return st;
     st = spmspv_launches(A, ctx->c, ctx->stream, mode, sr, x_nnz, d_x_idx, d_x_val, d_mask, complement_mask, path,
-                         th3, d_y_idx, d_y_val, d_y_nnz, ctx->single, [ctx](int cls, auto &&launch) -> dbs_status {
+                         th3, d_y_idx, d_y_val, d_y_nnz, ctx->single, stats != nullptr, [ctx](int cls, auto &&launch) -> dbs_status {
                              Timer t_(ctx, cls);
                              const hipError_t e = launch();
                              if (e != hipSuccess) {
@@ -881,7 +982,7 @@ extern "C" dbs_status dbs_spmspv_noalloc(const dbs_matrix *A, dbs_semiring sr, i
     if ((st = noalloc_device(s, &d)) != DBS_OK) return st;
     DevCtx c = noalloc_ctx(*d);
     st = spmspv_launches(A, c, s, mode, sr, x_nnz, d_x_idx, d_x_val, d_mask, complement_mask, path, th3, d_y_idx,
-                         d_y_val, d_y_nnz, false, [](int, auto &&launch) -> dbs_status {
+                         d_y_val, d_y_nnz, false, false, [](int, auto &&launch) -> dbs_status {
                              const hipError_t e = launch();
                              return e == hipSuccess ? DBS_OK : hip_fail(e, "kernel launch");
                          });

@@ -254,6 +254,52 @@ uint64_t inline_desc(const Entry *e, uint32_t nnz, const void *vals, uint32_t vb
     return d;
 }
 
+// Row-entry view: the CSR's own entries in row order, ascending columns (the
+// input's order within a row is free), with the row starts marked.
+void build_row_entries(dbs_host_matrix *h, const int64_t *row_ptr, const int32_t *col_idx, const void *vals,
+                       uint32_t vb)
+{
+    const int64_t nnz = h->nnz;
+    h->nre_chunk = (nnz + RE_CHUNK - 1) / RE_CHUNK;
+    h->re_col.reset(new uint32_t[(size_t)h->nre_chunk * RE_CHUNK]);
+    if (vb) h->re_val.reset(new uint8_t[(size_t)nnz * vb]);
+    uint32_t *col = h->re_col.get();
+    uint8_t *val = h->re_val.get();
+    parallel_chunks(h->m, 4096, [&](int, int64_t s, int64_t e) {
+        const int64_t a = row_ptr[s], b = row_ptr[e];
+        if (b > a) {
+            std::memcpy(col + a, col_idx + a, (size_t)(b - a) * 4);
+            if (vb) std::memcpy(val + a * vb, (const uint8_t *)vals + a * vb, (size_t)(b - a) * vb);
+        }
+        std::vector<std::pair<uint32_t, int64_t>> tmp;
+        for (int64_t i = s; i < e; ++i) {
+            const int64_t p = row_ptr[i], q = row_ptr[i + 1];
+            if (p == q) continue;
+            if (!std::is_sorted(col + p, col + q)) {
+                tmp.clear();
+                for (int64_t t = p; t < q; ++t) tmp.emplace_back((uint32_t)col_idx[t], t);
+                std::sort(tmp.begin(), tmp.end());
+                for (int64_t t = p; t < q; ++t) {
+                    col[t] = tmp[(size_t)(t - p)].first;
+                    if (vb) put_value(val + t * vb, vals, tmp[(size_t)(t - p)].second, vb);
+                }
+            }
+            col[p] |= RE_START;
+        }
+    });
+    for (int64_t t = nnz; t < h->nre_chunk * RE_CHUNK; ++t) col[t] = 0u;
+    // the rows that hold entries; per chunk the index among them of the row
+    // that the entry before the chunk belongs to
+    h->re_chord.assign((size_t)h->nre_chunk + 1, -1);
+    for (int32_t i = 0; i < h->m; ++i) {
+        const int64_t p = row_ptr[i], q = row_ptr[i + 1];
+        if (p == q) continue;
+        const int32_t o = (int32_t)h->re_row.size();
+        h->re_row.push_back(i);
+        for (int64_t c = p / RE_CHUNK + 1; c * RE_CHUNK <= q; ++c) h->re_chord[(size_t)c] = o;
+    }
+}
+
 struct RowBlockSizes {
     int64_t nblk = 0, bytes = 0, nseg = 0;
 };
@@ -380,12 +426,16 @@ extern "C" dbs_status dbs_host_build_csr(int32_t m, int32_t n, int64_t nnz, cons
         std::vector<std::vector<Entry>> scratch(nt);
         std::vector<std::array<int64_t, DBS_NUM_BLOCK_TYPES>> tcount(nt);
         for (auto &a : tcount) a.fill(0);
+        std::vector<int64_t> tcoo(nt, 0);  // entries in COO blocks
         parallel_chunks(nbr, 64, [&](int t, int64_t s, int64_t e) {
             for (int64_t R = s; R < e && !fail.failed.load(); ++R) {
                 if (!gather_block_row((int32_t)R, m, n, row_ptr, col_idx, scratch[t], fail)) return;
                 RowBlockSizes rs = walk_block_row(
                     scratch[t], o, vb,
-                    [&](size_t, uint32_t, uint32_t type, uint64_t, int32_t) { tcount[t][type]++; },
+                    [&](size_t, uint32_t bn, uint32_t type, uint64_t, int32_t) {
+                        tcount[t][type]++;
+                        if (type == T_COO) tcoo[t] += bn;
+                    },
                     [](int64_t, uint32_t) {});
                 rb_nblk[R + 1] = rs.nblk;
                 rb_bytes[R + 1] = rs.bytes;
@@ -457,6 +507,11 @@ extern "C" dbs_status dbs_host_build_csr(int32_t m, int32_t n, int64_t nnz, cons
             delete h;
             return dbs_fail(fail.st, "%s", fail.msg.c_str());
         }
+
+        // ---- row-entry view ----
+        int64_t ncoo = 0;
+        for (const int64_t c : tcoo) ncoo += c;
+        if (row_entries_wanted(nnz, ncoo, o.force_type)) build_row_entries(h, row_ptr, col_idx, vals, vb);
 
         // ---- block-CSC view by a counting sort over blocks ----
         const int32_t nbc = h->nbc;

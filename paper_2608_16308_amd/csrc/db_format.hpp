@@ -116,6 +116,12 @@ DBS_HD uint32_t record_align(uint32_t type, uint32_t vbytes)
     return type == T_COO ? (vbytes > 1 ? vbytes : 1u) : 16u;
 }
 
+// Entries per chunk of the row-entry view: whole wave steps of 64, and the
+// grain at which its rows can be found.
+constexpr int32_t RE_CHUNK = 256;
+// Column word of the row-entry view: bit 31 marks the first entry of a row.
+constexpr uint32_t RE_START = 1u << 31;
+
 // Pull segment weights by format (Sec. 3.3.2): Dense 4, ForceCSR / ForceCSC /
 // patched CSR 2, COO 1.
 DBS_HD uint32_t seg_weight(uint32_t type)

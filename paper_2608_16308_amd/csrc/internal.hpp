@@ -2,6 +2,7 @@
 #pragma once
 #include <cstdarg>
 #include <cstdint>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -30,8 +31,24 @@ struct dbs_host_matrix {
     // rows that hold at least one entry
     std::vector<uint32_t> row_occ;
     std::vector<uint8_t> payload;
+    // Row-entry view (see DevMatrix; empty when the matrix has none): the
+    // entries in row order with ascending columns.
+    std::unique_ptr<uint32_t[]> re_col;  // nre_chunk * RE_CHUNK words
+    std::unique_ptr<uint8_t[]> re_val;   // nnz values (NULL for a pattern)
+    std::vector<int32_t> re_row, re_chord;
+    int64_t nre_chunk = 0;
 };
 
 inline uint32_t dtype_bytes(dbs_dtype t) { return t == DBS_F32 ? 4u : (t == DBS_F16 ? 2u : 0u); }
+
+// Whether a matrix gets a row-entry view: it is a list of short COO blocks
+// more than a matrix of filled ones (at least half of its entries in COO
+// blocks), was not asked to hold one block format, and its entry positions
+// fit 32 bits.
+inline bool row_entries_wanted(int64_t nnz, int64_t coo_entries, int32_t force_type)
+{
+    return nnz > 0 && 2 * coo_entries >= nnz && force_type < 0 &&
+           nnz <= (int64_t)INT32_MAX - dbs::RE_CHUNK;
+}
 
 void fill_info(const dbs_host_matrix &h, dbs_matrix_info *out);

@@ -2727,6 +2727,8 @@ __global__ __launch_bounds__(FTPB) void k_finalize(uint32_t *__restrict__ ybits,
         counters[C_ERR_LAST] = (bad ? 1 : 0) | (pop < k - bad ? 2 : 0);
         counters[C_XBAD] = 0;
         counters[C_XPOP] = 0;
+        counters[C_EITEMS] = 0;
+        counters[C_EITEMS + 1] = 0;
     }
     (void)m;
 }

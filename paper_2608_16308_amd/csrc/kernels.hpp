@@ -48,6 +48,24 @@ struct DevMatrix {
     // no edge leads to them, and the pull levels then skip whole block rows
     // sooner.
     const uint32_t *row_occ = nullptr;
+    // Row-entry view (re_nchunk = 0: the matrix has none): every entry in row
+    // order with ascending columns -- the column word (bit 31: first entry of
+    // its row) and the value -- padded to whole chunks of RE_CHUNK entries;
+    // re_row lists the rows that hold entries; re_chord[c] is the index among
+    // them of the row of the entry before chunk c (-1 for the first chunk).
+    // Pull streams it (k_entry_pull) when most entries sit in short COO
+    // blocks, whose slot and descriptor words outweigh the entries.
+    const uint32_t *re_col = nullptr;
+    const void *re_val = nullptr;
+    const int32_t *re_row = nullptr;
+    const int32_t *re_chord = nullptr;
+    int32_t re_nnz = 0, re_nchunk = 0;
+    // Column-entry view (with the row-entry view): the rows and values of
+    // each column's entries, column j's at ce_ptr[j] .. ce_ptr[j + 1] - 1 in
+    // no fixed order.  Push walks the listed columns there (k_entry_push).
+    const int32_t *ce_ptr = nullptr;  // n + 1
+    const int32_t *ce_row = nullptr;
+    const void *ce_val = nullptr;
 };
 
 // Segments per segment-loop task: two wave iterations of 16 segments.
@@ -66,7 +84,8 @@ enum Counter : int {
     C_NTB = 8,       // push work items (nonzero vector blocks with a nonempty block column)
     C_XPOP = 9,      // distinct x indices (mask popcounts), summed by the scan tiles
     C_SYNCERR = 10,  // single launch: a bounded wait for other workgroups ran out
-    C_COUNT = 12
+    C_EITEMS = 12,   // (64 bits) push items and tasks over the column-entry view (k_entry_scatter)
+    C_COUNT = 14
 };
 constexpr int PATH_PUSH = 1, PATH_PULL = 2;
 #ifndef HV_CHUNK_BLOCKS
@@ -170,6 +189,26 @@ hipError_t launch_scan_dense(const DevMatrix &A, DevCtx &C, int mode, const void
 hipError_t launch_main(const DevMatrix &A, const DevCtx &C, int mode, const void *xd,
                        const uint32_t *omask, int complement, int32_t *parent, int forced_path,
                        hipStream_t s);
+// Traversals over the entry views (A.re_nchunk > 0), any mode but BFS.  None
+// of them writes the call's counters.
+//   launch_entry_scatter  blocker that also lists push items (into C.items:
+//                         at most one per x index), as push and auto need
+//   launch_entry_pull     pull; scanned: a scan ran, and the kernel returns
+//                         at once when its choice is push
+//   launch_entry_push     push
+//   launch_entry_auto     the choice is taken on the device
+hipError_t launch_entry_scatter(const DevMatrix &A, const DevCtx &C, int mode, int32_t k, const int32_t *x_idx,
+                                const void *x_val, hipStream_t s);
+hipError_t launch_entry_pull(const DevMatrix &A, const DevCtx &C, int mode, const uint32_t *omask, int complement,
+                             bool scanned, hipStream_t s);
+hipError_t launch_entry_push(const DevMatrix &A, const DevCtx &C, int mode, const uint32_t *omask, int complement,
+                             hipStream_t s);
+hipError_t launch_entry_auto(const DevMatrix &A, const DevCtx &C, int mode, const uint32_t *omask, int complement,
+                             double th3, double th3s, hipStream_t s);
+// Column-entry view from the row-entry view: entries per column (cnt zeroed
+// before), then their rows and values at next[column]++ (vb value bytes).
+hipError_t launch_ce_count(const DevMatrix &A, int32_t *cnt, hipStream_t s);
+hipError_t launch_ce_fill(const DevMatrix &A, int32_t vb, int32_t *next, int32_t *ce_row, void *ce_val, hipStream_t s);
 hipError_t launch_finalize(const DevMatrix &A, DevCtx &C, int mode, int32_t *y_idx,
                            void *y_val, int32_t *y_nnz, const int32_t *x_idx, int32_t k,
                            hipStream_t s);
