@@ -82,6 +82,11 @@ typedef enum { DBS_PATH_AUTO = 0, DBS_PATH_PUSH = 1, DBS_PATH_PULL = 2 } dbs_pat
 #define DBS_TH3_PAPER 0.01f
 #define DBS_TH3_SPREAD 0.12f
 #define DBS_BFS_PUSH_TASKS 0.1f
+/* The same rule for matrices that carry entry views (pattern matrices and
+ * matrices of short COO blocks built from CSR on the host, no forced block
+ * format): push iff the frontier's columns hold fewer entries than this share
+ * of the matrix's.                                                        */
+#define DBS_BFS_PUSH_ENTRIES 0.02f
 
 /* Low-level block formats (Sec. 3.2.1). */
 typedef enum {

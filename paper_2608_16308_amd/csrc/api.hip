@@ -104,6 +104,10 @@ struct dbs_ctx {
     // accumulator sets, allocated by the first batched call
     void *xdb = nullptr;
     double *yaccb = nullptr;
+    // BFS over the entry views: device scratch and the pinned copy of its
+    // record (bfs.vis NULL: not allocated)
+    DevBfs bfs;
+    BfsRecord *h_rec = nullptr;
 };
 
 namespace {
@@ -329,7 +333,7 @@ extern "C" dbs_status dbs_matrix_upload(const dbs_host_matrix *h, dbs_matrix **o
     if (h->nre_chunk > 0) {
         const size_t ncol = (size_t)h->nre_chunk * RE_CHUNK, vbytes = (size_t)h->nnz * dtype_bytes(h->dtype);
         const uint8_t *rv = nullptr;
-        if ((s2 = dev_upload(A->allocs, h->re_col.get(), ncol, &d.re_col)) != DBS_OK ||
+        if ((s2 = dev_upload(A->allocs, h->re_col.get(), ncol, &d.re_col, 64)) != DBS_OK ||
             (s2 = dev_upload(A->allocs, h->re_val.get(), vbytes, &rv)) != DBS_OK ||
             (s2 = dev_upload(A->allocs, h->re_row, &d.re_row)) != DBS_OK ||
             (s2 = dev_upload(A->allocs, h->re_chord, &d.re_chord)) != DBS_OK) {
@@ -338,6 +342,16 @@ extern "C" dbs_status dbs_matrix_upload(const dbs_host_matrix *h, dbs_matrix **o
             return s2;
         }
         d.re_val = rv;
+        d.re_sparse = h->re_sparse;
+        if (!h->re_info.empty()) {
+            const uint64_t *ri = nullptr;
+            if ((s2 = dev_upload(A->allocs, h->re_info, &ri)) != DBS_OK) {
+                free_all(A->allocs);
+                delete A;
+                return s2;
+            }
+            d.re_info = (const int2 *)ri;
+        }
         d.re_nnz = (int32_t)h->nnz;
         d.re_nchunk = (int32_t)h->nre_chunk;
         if ((s2 = column_entries(A)) != DBS_OK) {
@@ -420,6 +434,8 @@ extern "C" void dbs_matrix_destroy(dbs_matrix *A)
 // ---------------------------------------------------------------------------
 // context
 // ---------------------------------------------------------------------------
+static bool bfs_scratch(dbs_ctx *ctx);
+
 extern "C" dbs_status dbs_ctx_create(const dbs_matrix *sizing, void *stream, dbs_ctx **out)
 {
     if (!sizing || !out) return dbs_fail(DBS_ERR_ARG, "dbs_ctx_create: NULL argument");
@@ -479,8 +495,43 @@ extern "C" dbs_status dbs_ctx_create(const dbs_matrix *sizing, void *stream, dbs
         delete ctx;
         return hip_fail(e, "hipHostMalloc");
     }
+    if (sizing->d.re_info && sizing->d.dtype == DBS_PATTERN) (void)bfs_scratch(ctx);
     *out = ctx;
     return DBS_OK;
+}
+
+// BFS scratch for the context's largest column count; false (and nothing
+// kept) when memory runs out.  A context sized by a pattern matrix has it from
+// the start, others from their first BFS.
+static bool bfs_scratch(dbs_ctx *ctx)
+{
+    if (ctx->bfs.vis) return true;
+    DevBfs b;
+    BfsRecord *rec = nullptr;
+    const size_t n = (size_t)std::max(ctx->max_n, 1), words = ((n + 31) / 32 + 63) / 64 * 64;
+    uint8_t *p = nullptr;
+    const size_t small = 256 + ((sizeof(BfsRecord) + 255) & ~(size_t)255);
+    if (hipMalloc((void **)&p, small + 4 * words * 4 + 2 * n * sizeof(int4)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (hipHostMalloc((void **)&rec, sizeof(BfsRecord), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipFree(p);
+        return false;
+    }
+    ctx->allocs.push_back(p);
+    ctx->h_rec = rec;
+    static_assert(4 * sizeof(BfsCount) <= 256, "BFS counts");
+    b.cnt = (BfsCount *)p;
+    b.rec = (BfsRecord *)(p + 256);
+    uint32_t *w = (uint32_t *)(p + small);
+    b.vis = w;
+    for (int i = 0; i < 3; ++i) b.bits[i] = w + (size_t)(i + 1) * words;
+    b.items[0] = (int4 *)(w + 4 * words);
+    b.items[1] = b.items[0] + n;
+    ctx->bfs = b;
+    return true;
 }
 
 extern "C" dbs_status dbs_ctx_set_stream(dbs_ctx *ctx, void *stream)
@@ -503,6 +554,7 @@ extern "C" void dbs_ctx_destroy(dbs_ctx *ctx)
     if (ctx->xdb) (void)hipFree(ctx->xdb);
     if (ctx->yaccb) (void)hipFree(ctx->yaccb);
     if (ctx->h_counters) (void)hipHostFree(ctx->h_counters);
+    if (ctx->h_rec) (void)hipHostFree(ctx->h_rec);
     delete ctx;
 }
 
@@ -624,7 +676,7 @@ dbs_status spmspv_launches(const dbs_matrix *A, DevCtx &c, hipStream_t s, int mo
     // fit the item list up to one index per vector block; an automatic choice
     // of push with the default th3 has at most a quarter of that).  No scan
     // runs; only a call that asks for statistics lets one count afterwards.
-    const bool entries = A->d.re_nchunk > 0;
+    const bool entries = A->d.re_nchunk > 0 && A->d.re_sparse;
     const bool items = entries && launch_path != DBS_PATH_PULL && x_nnz <= A->d.nbc;
     if (items || (entries && launch_path == DBS_PATH_PULL)) {
         st = run(DBS_K_SCATTER, [&] {
@@ -815,6 +867,40 @@ extern "C" dbs_status dbs_bfs(dbs_ctx *ctx, const dbs_matrix *A, int32_t source,
     if (policy < DBS_PATH_AUTO || policy > DBS_PATH_PULL) return dbs_fail(DBS_ERR_ARG, "unknown path");
     const hipStream_t s = ctx->stream;
     if (stats) std::memset(stats, 0, sizeof *stats);
+    // (a pattern of filled blocks pulls faster over its blocks, whose masks are
+    // an eighth of the entries: where pull is asked for, it stays there)
+    const bool blocks = !A->d.re_sparse && (policy == DBS_PATH_PULL || (policy == DBS_PATH_AUTO && th3 > 0.f));
+    if (A->d.re_info && !blocks && bfs_scratch(ctx)) {
+        // over the entry views: a kernel per level, launched ahead of the
+        // host, which looks after the first BFS_AHEAD levels and then after
+        // every half as many more (a level past the end returns at once)
+        constexpr int32_t BFS_AHEAD = 8;
+        LAUNCH(ctx, DBS_K_OTHER, launch_bfs_start(A->d, ctx->bfs, source, d_level, d_parent, s));
+        const BfsRecord *r = ctx->h_rec;
+        for (int32_t l = 0, until = BFS_AHEAD;; until = l + std::max(4, std::min(l / 2, 64))) {
+            for (; l < until; ++l)
+                LAUNCH(ctx, DBS_K_MAIN,
+                       launch_bfs_level(A->d, ctx->bfs, l, d_level, d_parent, (int)policy, th3 > 0.f ? (double)th3 : 0.0,
+                                        (double)DBS_BFS_PUSH_ENTRIES, s));
+            hipError_t e = hipMemcpyAsync(ctx->h_rec, ctx->bfs.rec, sizeof(BfsRecord), hipMemcpyDeviceToHost, s);
+            if (e == hipSuccess) e = hipStreamSynchronize(s);
+            if (e != hipSuccess) {
+                ctx->broken = true;
+                return hip_fail(e, "BFS record");
+            }
+            if (r->levels < l) break;
+        }
+        if (stats) {
+            stats->levels = r->levels;
+            stats->reached = r->reached;
+            static_assert(BFS_RECORD_LEVELS == DBS_BFS_MAX_LEVEL_STATS, "BFS level statistics");
+            for (int32_t i = 0; i < std::min(r->levels, BFS_RECORD_LEVELS); ++i) {
+                stats->path[i] = r->path[i];
+                stats->frontier[i] = r->frontier[i];
+            }
+        }
+        return DBS_OK;
+    }
     LAUNCH(ctx, DBS_K_OTHER, launch_bfs_init(A->d, ctx->c, source, d_level, d_parent, s));
     int32_t level = 0, reached = 1, frontier = 1;
     for (;;) {

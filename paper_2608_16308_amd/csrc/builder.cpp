@@ -298,6 +298,15 @@ void build_row_entries(dbs_host_matrix *h, const int64_t *row_ptr, const int32_t
         h->re_row.push_back(i);
         for (int64_t c = p / RE_CHUNK + 1; c * RE_CHUNK <= q; ++c) h->re_chord[(size_t)c] = o;
     }
+    if (h->m != h->n) return;
+    h->re_info.resize((size_t)h->m + 1);
+    parallel_chunks((int64_t)h->m + 1, 65536, [&](int, int64_t s, int64_t e) {
+        for (int64_t i = s; i < e; ++i) {
+            const int64_t p = row_ptr[i];
+            const uint64_t first = p < nnz ? col[p] & ~RE_START : 0u;
+            h->re_info[(size_t)i] = (uint64_t)p | first << 32;
+        }
+    });
 }
 
 struct RowBlockSizes {
@@ -511,7 +520,8 @@ extern "C" dbs_status dbs_host_build_csr(int32_t m, int32_t n, int64_t nnz, cons
         // ---- row-entry view ----
         int64_t ncoo = 0;
         for (const int64_t c : tcoo) ncoo += c;
-        if (row_entries_wanted(nnz, ncoo, o.force_type)) build_row_entries(h, row_ptr, col_idx, vals, vb);
+        h->re_sparse = entries_sparse(nnz, ncoo, o.force_type);
+        if (entries_wanted(nnz, h->re_sparse, vt, o.force_type)) build_row_entries(h, row_ptr, col_idx, vals, vb);
 
         // ---- block-CSC view by a counting sort over blocks ----
         const int32_t nbc = h->nbc;

@@ -48,11 +48,10 @@ __device__ __forceinline__ bool ev_admit(const uint32_t *omask, int32_t compleme
 // The values and mask bits of k_scatter; besides, every distinct index whose
 // column holds entries becomes a work item {first task, entry - first task,
 // x bits, 0}, its tasks being the column's entries.  A workgroup reserves its
-// items and tasks with one 64-bit atomic (tasks in the low 40 bits), so that
+// items and tasks with one 64-bit atomic, so that
 // items ascend in their first tasks without a scan over the workgroups.  A
 // repeated index keeps the occurrence whose mask atomic found its bit clear.
 constexpr int ES_TPB = 256;
-constexpr int EV_TASK_BITS = 40;
 
 template <int MODE>
 __global__ __launch_bounds__(ES_TPB) void k_entry_scatter(const int32_t *__restrict__ xi, const void *__restrict__ xv,
@@ -91,12 +90,14 @@ __global__ __launch_bounds__(ES_TPB) void k_entry_scatter(const int32_t *__restr
     // runs of consecutive lanes with one mask word: one returning atomic each
     const uint32_t w = ok ? (uint32_t)j >> 5 : 0xFFFFFFFFu;
     const uint32_t bit = ok ? 1u << (j & 31) : 0u;
-    const bool head = lane == 0 || dpp_mov<dppc::WF_SR1>(~w, w) != w;
+    const uint32_t wp = dpp_mov<dppc::WF_SR1>(~w, w);  // (every lane active, here and below)
+    const bool head = lane == 0 || wp != w;
     const uint64_t heads = ballot(head);
     const uint64_t upto = lane == WAVE - 1 ? ~0ull : (1ull << (lane + 1)) - 1ull;
     const uint32_t run = (uint32_t)__popcll(heads & upto);
     const uint32_t incl = wave_run_or(bit, run);
-    const uint32_t excl = head ? 0u : dpp_mov<dppc::WF_SR1>(0u, incl);
+    const uint32_t ip = dpp_mov<dppc::WF_SR1>(0u, incl);
+    const uint32_t excl = head ? 0u : ip;
     const uint64_t above = heads & ~upto;
     const int last = above ? ctz64(above) - 1 : WAVE - 1;
     uint32_t old = 0;

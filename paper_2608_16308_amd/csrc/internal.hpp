@@ -36,19 +36,25 @@ struct dbs_host_matrix {
     std::unique_ptr<uint32_t[]> re_col;  // nre_chunk * RE_CHUNK words
     std::unique_ptr<uint8_t[]> re_val;   // nnz values (NULL for a pattern)
     std::vector<int32_t> re_row, re_chord;
+    std::vector<uint64_t> re_info;       // square matrices: first entry | its column << 32
+    bool re_sparse = false;
     int64_t nre_chunk = 0;
 };
 
 inline uint32_t dtype_bytes(dbs_dtype t) { return t == DBS_F32 ? 4u : (t == DBS_F16 ? 2u : 0u); }
 
-// Whether a matrix gets a row-entry view: it is a list of short COO blocks
-// more than a matrix of filled ones (at least half of its entries in COO
-// blocks), was not asked to hold one block format, and its entry positions
-// fit 32 bits.
-inline bool row_entries_wanted(int64_t nnz, int64_t coo_entries, int32_t force_type)
+// Whether SpMSpV runs over the entry views: the matrix is a list of short COO
+// blocks more than one of filled blocks (at least half of its entries sit in
+// COO blocks) and was not asked to hold one block format.
+inline bool entries_sparse(int64_t nnz, int64_t coo_entries, int32_t force_type)
 {
-    return nnz > 0 && 2 * coo_entries >= nnz && force_type < 0 &&
-           nnz <= (int64_t)INT32_MAX - dbs::RE_CHUNK;
+    return 2 * coo_entries >= nnz && force_type < 0;
+}
+// Whether a matrix gets entry views (entry positions fit 32 bits): for
+// SpMSpV, or, a pattern, for BFS.
+inline bool entries_wanted(int64_t nnz, bool sparse, int32_t dtype, int32_t force_type)
+{
+    return nnz > 0 && nnz <= (int64_t)INT32_MAX - dbs::RE_CHUNK && (sparse || (dtype == DBS_PATTERN && force_type < 0));
 }
 
 void fill_info(const dbs_host_matrix &h, dbs_matrix_info *out);

@@ -66,6 +66,39 @@ struct DevMatrix {
     const int32_t *ce_ptr = nullptr;  // n + 1
     const int32_t *ce_row = nullptr;
     const void *ce_val = nullptr;
+    // SpMSpV runs over the entry views (most entries sit in short COO
+    // blocks); a pattern matrix of filled blocks has the views for BFS only.
+    bool re_sparse = false;
+    // BFS, square matrices: {first entry, its column} per row and the end
+    // (m + 1; a row without entries repeats the next row's first entry).
+    const int2 *re_info = nullptr;
+};
+
+// Push work items and tasks share a 64-bit count: tasks in the low bits.
+constexpr int EV_TASK_BITS = 32;
+
+// BFS over the entry views.  BfsCount: the vertices found for one level --
+// items << EV_TASK_BITS | column entries of those listed as push items, the
+// number of the others, whether the list is incomplete, and the nonzero
+// vector blocks (kept only when the selector asks for them).  BfsRecord: what
+// the host reads.
+struct BfsCount {
+    uint64_t items;
+    uint64_t ent;         // entries of the others
+    uint64_t seen, prev;  // entries of all levels before, and of the one before
+    uint32_t extra, inc, nvb, pad;
+};
+constexpr int BFS_RECORD_LEVELS = 64;
+struct BfsRecord {
+    int32_t levels, reached;
+    int32_t path[BFS_RECORD_LEVELS], frontier[BFS_RECORD_LEVELS];
+};
+// Scratch, written afresh by every BFS.
+struct DevBfs {
+    uint32_t *vis = nullptr, *bits[3] = {nullptr, nullptr, nullptr};
+    int4 *items[2] = {nullptr, nullptr};
+    BfsCount *cnt = nullptr;  // 4: three in turn, one for a list rebuilt
+    BfsRecord *rec = nullptr;
 };
 
 // Segments per segment-loop task: two wave iterations of 16 segments.
@@ -232,6 +265,13 @@ hipError_t launch_rows_batch(const DevMatrix &A, const DevCtx &C, int mode, int3
                              double *yaccb, hipStream_t s);
 hipError_t launch_finalize_batch(const DevMatrix &A, const DevCtx &C, int mode, int32_t nb, int32_t NB,
                                  double *yaccb, void *y, float *y32, hipStream_t s);
+// BFS over the entry views (A.re_info): the start, then one launch per level;
+// a level after the last returns at once.  policy 0 with th3 <= 0 pushes
+// while the frontier's columns hold less than push_share of the entries.
+hipError_t launch_bfs_start(const DevMatrix &A, const DevBfs &B, int32_t source, int32_t *level, int32_t *parent,
+                            hipStream_t s);
+hipError_t launch_bfs_level(const DevMatrix &A, const DevBfs &B, int32_t l, int32_t *level, int32_t *parent,
+                            int policy, double th3, double push_share, hipStream_t s);
 hipError_t launch_bfs_init(const DevMatrix &A, const DevCtx &C, int32_t source, int32_t *level,
                            int32_t *parent, hipStream_t s);
 hipError_t launch_bfs_update(const DevMatrix &A, const DevCtx &C, int32_t next_level,
