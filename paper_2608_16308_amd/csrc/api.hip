@@ -44,8 +44,8 @@ dbs_status check_device()
     return DBS_OK;
 }
 
-// pad: zeroed bytes after the data (the payload gets 16, so that a 16-byte
-// load of the chunk holding a record's last byte stays inside the allocation)
+// pad: zeroed bytes after the data (PAYLOAD_PAD for the payload: loads of whole
+// 16-byte chunks and value runs past a record's end stay inside the allocation)
 template <class T>
 dbs_status dev_upload(std::vector<void *> &allocs, const T *h, size_t count, const T **out, size_t pad = 0)
 {
@@ -187,8 +187,7 @@ dbs_status check_ctx(dbs_ctx *ctx, const dbs_matrix *A)
 // ---------------------------------------------------------------------------
 // matrix
 // ---------------------------------------------------------------------------
-// The column-entry view of a matrix that has its row-entry view.
-static dbs_status column_entries(dbs_matrix *A)
+dbs_status column_entries(dbs_matrix *A)
 {
     DevMatrix &d = A->d;
     const int32_t vb = (int32_t)dtype_bytes((dbs_dtype)d.dtype);
@@ -323,7 +322,7 @@ extern "C" dbs_status dbs_matrix_upload(const dbs_host_matrix *h, dbs_matrix **o
         (s2 = dev_upload(A->allocs, hv_cstart, &d.hv_cstart)) != DBS_OK ||
         (s2 = dev_upload(A->allocs, hv_crow, &d.hv_crow)) != DBS_OK ||
         (s2 = dev_upload(A->allocs, hv_rowchunks, &d.hv_rowchunks)) != DBS_OK ||
-        (s2 = dev_upload(A->allocs, h->payload, &d.pay, 16)) != DBS_OK ||
+        (s2 = dev_upload(A->allocs, h->payload, &d.pay, PAYLOAD_PAD)) != DBS_OK ||
         (s2 = dev_upload(A->allocs, task_order, &d.task_order)) != DBS_OK ||
         (s2 = dev_upload(A->allocs, h->row_occ, &d.row_occ)) != DBS_OK) {
         free_all(A->allocs);
@@ -355,6 +354,38 @@ extern "C" dbs_status dbs_matrix_upload(const dbs_host_matrix *h, dbs_matrix **o
         d.re_nnz = (int32_t)h->nnz;
         d.re_nchunk = (int32_t)h->nre_chunk;
         if ((s2 = column_entries(A)) != DBS_OK) {
+            free_all(A->allocs);
+            delete A;
+            return s2;
+        }
+    }
+    if (h->nblk > 0 && h->dtype != DBS_PATTERN && h->nnz >= BLOCK_LIST_ENTRIES * h->nblk) {
+        std::vector<int32_t> col, ptr;
+        std::vector<uint64_t> desc;
+        try {
+            col.resize((size_t)h->nblk);
+            desc.resize((size_t)h->nblk);
+            ptr.assign((size_t)h->nbr * MC_COUNT + 1, 0);
+            for (int32_t R = 0; R < h->nbr; ++R) {
+                int32_t *at = ptr.data() + (size_t)R * MC_COUNT, cnt[MC_COUNT] = {0, 0, 0, 0};
+                for (int32_t b = h->rb_ptr[R]; b < h->rb_ptr[R + 1]; ++b)
+                    ++cnt[mfma_class(desc_type(h->desc[b]), desc_nnz(h->desc[b]))];
+                for (int k = 0; k < MC_COUNT; ++k) at[k + 1] = at[k] + cnt[k];
+                int32_t to[MC_COUNT] = {at[0], at[1], at[2], at[3]};
+                for (int32_t b = h->rb_ptr[R]; b < h->rb_ptr[R + 1]; ++b) {
+                    const int32_t q = to[mfma_class(desc_type(h->desc[b]), desc_nnz(h->desc[b]))]++;
+                    col[(size_t)q] = h->cb_col[b];
+                    desc[(size_t)q] = h->desc[b];
+                }
+            }
+        } catch (const std::bad_alloc &) {
+            free_all(A->allocs);
+            delete A;
+            return dbs_fail(DBS_ERR_ALLOC, "host allocation failed during upload");
+        }
+        if ((s2 = dev_upload(A->allocs, col, &d.ab_col)) != DBS_OK ||
+            (s2 = dev_upload(A->allocs, desc, &d.ab_desc)) != DBS_OK ||
+            (s2 = dev_upload(A->allocs, ptr, &d.ab_rptr)) != DBS_OK) {
             free_all(A->allocs);
             delete A;
             return s2;
@@ -685,7 +716,7 @@ dbs_status spmspv_launches(const dbs_matrix *A, DevCtx &c, hipStream_t s, int mo
         });
         if (st != DBS_OK) return st;
         st = run(DBS_K_MAIN, [&] {
-            return launch_path == DBS_PATH_PULL   ? launch_entry_pull(A->d, c, mode, d_mask, cm, false, s)
+            return launch_path == DBS_PATH_PULL   ? launch_entry_pull(A->d, c, mode, d_mask, cm, false, false, s)
                    : launch_path == DBS_PATH_PUSH ? launch_entry_push(A->d, c, mode, d_mask, cm, s)
                                                   : launch_entry_auto(A->d, c, mode, d_mask, cm, t3, t3s, s);
         });
@@ -708,7 +739,7 @@ dbs_status spmspv_launches(const dbs_matrix *A, DevCtx &c, hipStream_t s, int mo
             if (st != DBS_OK) return st;
         }
         if (entries && launch_path == DBS_PATH_AUTO) {
-            st = run(DBS_K_MAIN, [&] { return launch_entry_pull(A->d, c, mode, d_mask, cm, true, s); });
+            st = run(DBS_K_MAIN, [&] { return launch_entry_pull(A->d, c, mode, d_mask, cm, true, false, s); });
             if (st != DBS_OK) return st;
             launch_path = DBS_PATH_PUSH;  // (the push kernel, if the device chose it)
         }
@@ -779,6 +810,24 @@ extern "C" dbs_status dbs_spmspv_dense(dbs_ctx *ctx, const dbs_matrix *A, const 
         // pull known on the host: the non-COO pass reads the activation
         // itself, without a scan, and writes y itself
         LAUNCH(ctx, DBS_K_MAIN, launch_rows_dx(A->d, ctx->c, mode, d_x_dense, d_y_dense, d_y_f32, s));
+    } else if (A->d.re_sparse && path != DBS_PATH_PUSH && !(path == DBS_PATH_AUTO && th3 > 0.f)) {
+        // short COO blocks: the row-entry view, whatever the selector would
+        // choose (the scan only counts and chooses for the statistics)
+        LAUNCH(ctx, DBS_K_SCATTER, launch_ballot(A->d, ctx->c, mode, d_x_dense, s));
+        LAUNCH(ctx, DBS_K_MAIN, launch_entry_pull(A->d, ctx->c, mode, nullptr, 0, false, true, s));
+        if (stats)
+            LAUNCH(ctx, DBS_K_SCAN, launch_scan(A->d, ctx->c, p, (double)norm_th3(th3), spread_th3(th3), s));
+        LAUNCH(ctx, DBS_K_FINALIZE, launch_finalize_dense(A->d, ctx->c, mode, d_y_dense, d_y_f32, s));
+    } else if (rows_mfma_fits(A->d) && path != DBS_PATH_PUSH && !(path == DBS_PATH_AUTO && th3 > 0.f)) {
+        // blocks of many entries: all of them on the matrix cores, whatever
+        // the selector would choose (a call that asks for statistics lets the
+        // scan count and choose afterwards, and clears what that wrote)
+        LAUNCH(ctx, DBS_K_MAIN, launch_rows_mfma(A->d, ctx->c, ctx->c.yacc, 1, d_x_dense, d_y_dense, d_y_f32, s));
+        if (stats) {
+            LAUNCH(ctx, DBS_K_SCATTER, launch_ballot(A->d, ctx->c, mode, d_x_dense, s));
+            LAUNCH(ctx, DBS_K_SCAN, launch_scan(A->d, ctx->c, p, (double)norm_th3(th3), spread_th3(th3), s));
+            LAUNCH(ctx, DBS_K_FINALIZE, launch_finalize_dense(A->d, ctx->c, mode, nullptr, nullptr, s));
+        }
     } else {
         if (scan_takes_dense(A->d, d_x_dense)) {
             LAUNCH(ctx, DBS_K_SCAN,
@@ -814,9 +863,13 @@ extern "C" dbs_status dbs_spmm_dense(dbs_ctx *ctx, const dbs_matrix *A, int32_t 
     if (!d_x || !d_y) return dbs_fail(DBS_ERR_ARG, "NULL activations or outputs");
     const int mode = A->d.dtype == DBS_F16 ? M_F16 : M_F32;
     const size_t vb = A->d.dtype == DBS_F16 ? 2 : 4;
-    if (nb == 1 || A->d.nheavy < A->d.nblk || A->d.nblk == 0) {
-        // one vector, or a matrix with COO blocks (their segment loop is
-        // single-vector): one dense-activation call per vector
+    // the matrix-core pass, but for two fp32 vectors on blocks that the shared
+    // pass below takes (11008 x 4096: 43 against 49 us)
+    const bool two_vec = nb == 2 && A->d.dtype == DBS_F32 && A->d.nheavy == A->d.nblk && A->d.nbr >= 256;
+    const bool mfma = nb > 1 && rows_mfma_fits(A->d) && !two_vec;
+    if (!mfma && (nb == 1 || A->d.nheavy < A->d.nblk || A->d.nblk == 0)) {
+        // one vector, or a matrix of COO blocks with few entries each (their
+        // segment loop is single-vector): one dense-activation call per vector
         for (int32_t b = 0; b < nb; ++b) {
             st = dbs_spmspv_dense(ctx, A, (const char *)d_x + (size_t)b * A->d.n * vb, DBS_PATH_AUTO, 0.f,
                                   (char *)d_y + (size_t)b * A->d.m * vb, d_y_f32 ? d_y_f32 + (size_t)b * A->d.m : nullptr,
@@ -825,7 +878,7 @@ extern "C" dbs_status dbs_spmm_dense(dbs_ctx *ctx, const dbs_matrix *A, int32_t 
         }
         return DBS_OK;
     }
-    if (!ctx->xdb) {
+    if (!ctx->xdb && (!mfma || stats || rows_mfma_parts(A->d) > 1)) {
         const size_t xb = (size_t)DBS_MAX_BATCH * BS * ctx->max_nbc * 4;
         const size_t yb = (size_t)DBS_MAX_BATCH * BS * ctx->max_nbr * sizeof(double);
         HIP_TRY(hipMalloc(&ctx->xdb, xb), "hipMalloc (batched x)");
@@ -835,10 +888,16 @@ extern "C" dbs_status dbs_spmm_dense(dbs_ctx *ctx, const dbs_matrix *A, int32_t 
     }
     const int32_t NB = nb <= 2 ? 2 : nb <= 4 ? 4 : 8;
     const hipStream_t s = ctx->stream;
-    LAUNCH(ctx, DBS_K_SCATTER, launch_ballot_batch(A->d, ctx->c, mode, d_x, nb, NB, ctx->xdb, s));
-    LAUNCH(ctx, DBS_K_SCAN, launch_scan(A->d, ctx->c, PATH_PULL, 0.0, 0.0, s));
-    LAUNCH(ctx, DBS_K_MAIN, launch_rows_batch(A->d, ctx->c, mode, NB, ctx->xdb, ctx->yaccb, s));
-    LAUNCH(ctx, DBS_K_FINALIZE, launch_finalize_batch(A->d, ctx->c, mode, nb, NB, ctx->yaccb, d_y, d_y_f32, s));
+    if (mfma) LAUNCH(ctx, DBS_K_MAIN, launch_rows_mfma(A->d, ctx->c, ctx->yaccb, nb, d_x, d_y, d_y_f32, s));
+    if (!mfma || stats) {
+        // (after the matrix-core pass: the masks, counted for the statistics
+        // and cleared again)
+        LAUNCH(ctx, DBS_K_SCATTER, launch_ballot_batch(A->d, ctx->c, mode, d_x, nb, NB, ctx->xdb, s));
+        LAUNCH(ctx, DBS_K_SCAN, launch_scan(A->d, ctx->c, PATH_PULL, 0.0, 0.0, s));
+        if (!mfma) LAUNCH(ctx, DBS_K_MAIN, launch_rows_batch(A->d, ctx->c, mode, NB, ctx->xdb, ctx->yaccb, s));
+        LAUNCH(ctx, DBS_K_FINALIZE,
+               launch_finalize_batch(A->d, ctx->c, mode, mfma ? 0 : nb, NB, ctx->yaccb, d_y, d_y_f32, s));
+    }
     if (stats) {
         if ((st = sync_counters(ctx)) != DBS_OK) return st;
         const int32_t *h = ctx->h_counters;

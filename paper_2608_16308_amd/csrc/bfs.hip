@@ -85,7 +85,7 @@ __device__ __forceinline__ bool bit_of(const uint32_t *b, uint32_t i) { return (
 template <class At>
 __device__ __forceinline__ void bfs_flush(BfsLds &L, BfsCount *next, int4 *items, int32_t n, At &&at)
 {
-    const int t = threadIdx.x, lane = lane_id(), wv = t >> 6;
+    const int t = threadIdx.x, lane = lane_id(), wv = wave_id();
     for (int32_t i0 = 0; i0 < n; i0 += BL_TPB) {
         const bool on = i0 + t < n;
         int32_t v = 0, p = 0, len = 0;
@@ -139,7 +139,7 @@ template <int G>
 __global__ __launch_bounds__(BL_TPB, 8) void k_bfs_level(BfsArgs a, int32_t l)
 {
     __shared__ BfsLds L;
-    const int t = threadIdx.x, lane = lane_id(), wv = t >> 6;
+    const int t = threadIdx.x, lane = lane_id(), wv = wave_id();
     const BfsCount c = a.cnt[l % 3];
     const uint32_t *F = a.bits[l % 3];
     uint32_t *nb = a.bits[(l + 1) % 3], *clr = a.bits[(l + 2) % 3];
@@ -463,7 +463,7 @@ __global__ __launch_bounds__(BL_TPB, 8) void k_bfs_stream(BfsArgs a, int32_t l, 
     __shared__ uint32_t q_col[BL_WAVES][BS_QUEUE], q_ord[BL_WAVES][BS_QUEUE];
     __shared__ uint64_t s_ent;
     __shared__ uint32_t s_found, s_nvb;
-    const int t = threadIdx.x, lane = lane_id(), wv = t >> 6;
+    const int t = threadIdx.x, lane = lane_id(), wv = wave_id();
     const BfsCount c = a.cnt[l % 3];
     if ((uint32_t)(c.items >> EV_TASK_BITS) + c.extra == 0 || !bfs_stream(a, c)) return;
     if (a.policy == 0 && (double)c.nvb < a.th3n) return;  // (push)

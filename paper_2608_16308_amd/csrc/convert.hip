@@ -32,7 +32,7 @@ using namespace dbs;
 namespace {
 
 constexpr int CTPB = 256;             // 4 waves per workgroup, one tile each
-constexpr int RS = 10;                // per-row statistics, see k_conv_rows
+constexpr int RS = 11;                // per-row statistics, see k_conv_rows
 constexpr int PRE = 5;                // per-row prefixes: blocks, bytes, segments, non-COO, chunks
 
 dbs_status conv_fail(hipError_t e, const char *what)
@@ -135,7 +135,8 @@ __global__ __launch_bounds__(CTPB) void k_conv_tiles(const void *w, int64_t ld, 
 // record offset within the row (all ones: inline), block index within the
 // row | position in its segment << 28, segment index within the row, index
 // among the row's non-COO blocks.  Per row (RS int64): blocks, payload bytes
-// (16-byte multiple), segments, non-COO blocks, nnz, blocks by type.
+// (16-byte multiple), segments, non-COO blocks, nnz, blocks by type, entries in
+// COO blocks.
 __global__ __launch_bounds__(CTPB) void k_conv_rows(const uint32_t *tinfo, int32_t nbr, int32_t nbc,
                                                     int32_t seg_close, uint32_t vb, uint32_t *toff, uint32_t *tb,
                                                     uint32_t *tseg, uint32_t *thv, int64_t *rstat)
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(CTPB) void k_conv_rows(const uint32_t *tinfo, int32
     if (R >= nbr) return;
     uint64_t cursor = 0;
     uint32_t seg_w = 0, seg_cnt = 0, nseg = 0, nblk = 0, heavy = 0;
-    int64_t nnz_sum = 0, bytype[DBS_NUM_BLOCK_TYPES] = {0, 0, 0, 0, 0};
+    int64_t nnz_sum = 0, coo = 0, bytype[DBS_NUM_BLOCK_TYPES] = {0, 0, 0, 0, 0};
     for (int32_t J = 0; J < nbc; ++J) {
         const int64_t tile = (int64_t)R * nbc + J;
         const uint32_t t = tinfo[tile];
@@ -170,6 +171,7 @@ __global__ __launch_bounds__(CTPB) void k_conv_rows(const uint32_t *tinfo, int32
         }
         ++nblk;
         nnz_sum += nnz;
+        coo += type == T_COO ? nnz : 0;
         bytype[type]++;
     }
     if (seg_cnt) ++nseg;
@@ -181,6 +183,7 @@ __global__ __launch_bounds__(CTPB) void k_conv_rows(const uint32_t *tinfo, int32
     o[4] = nnz_sum;
 #pragma unroll
     for (int t = 0; t < DBS_NUM_BLOCK_TYPES; ++t) o[5 + t] = bytype[t];
+    o[10] = coo;
 }
 
 struct ConvOut {
@@ -190,6 +193,7 @@ struct ConvOut {
     int32_t *hv_col;
     uint64_t *hv_desc;
     uint64_t *blk_desc;  // descriptor per primary block (for the CSC fill)
+    int32_t *blk_col;    // block column per primary block (NULL: not wanted)
 };
 
 // A wave per nonzero tile: record, descriptor, slot, non-COO list entry.
@@ -304,12 +308,43 @@ __global__ __launch_bounds__(CTPB) void k_conv_write(const void *w, int64_t ld, 
         out.sl_col[slot] = slot_word(J, d);
         out.sl_desc[slot] = d;
         out.blk_desc[b] = d;
+        if (out.blk_col) out.blk_col[b] = J;
         if (type != T_COO) {
             const int64_t hv = P[3] + (int64_t)thv[tile];
             out.hv_col[hv] = J;
             out.hv_desc[hv] = d;
         }
     }
+}
+
+// A wave per block row: its blocks by class (mfma_class), in block-CSR order
+// within a class.
+__global__ __launch_bounds__(CTPB) void k_conv_list(int32_t nbr, const int64_t *pre, const int32_t *blk_col,
+                                                    const uint64_t *blk_desc, int32_t *ab_col, uint64_t *ab_desc,
+                                                    int32_t *ab_rptr)
+{
+    const int lane = lane_id();
+    const int32_t R = (int32_t)(blockIdx.x * (CTPB / WAVE) + (threadIdx.x >> 6));
+    if (R >= nbr) return;
+    const int64_t b0 = pre[(int64_t)R * PRE], b1 = pre[(int64_t)(R + 1) * PRE];
+    const uint64_t below = (1ull << lane) - 1ull;
+    int64_t to = b0;
+    for (int k = 0; k < MC_COUNT; ++k) {
+        if (lane == 0) ab_rptr[(int64_t)R * MC_COUNT + k] = (int32_t)to;
+        for (int64_t b = b0; b < b1; b += WAVE) {
+            const bool in = b + lane < b1;
+            const uint64_t d = in ? blk_desc[b + lane] : 0ull;
+            const bool mine = in && mfma_class(desc_type(d), desc_nnz(d)) == k;
+            const uint64_t m = ballot(mine);
+            if (mine) {
+                const int64_t q = to + __popcll(m & below);
+                ab_col[q] = blk_col[b + lane];
+                ab_desc[q] = d;
+            }
+            to += __popcll(m);
+        }
+    }
+    if (R == nbr - 1 && lane == 0) ab_rptr[(int64_t)nbr * MC_COUNT] = (int32_t)b1;
 }
 
 // A thread per block row: its segment words (the block row) and non-COO
@@ -333,6 +368,54 @@ __global__ __launch_bounds__(CTPB) void k_conv_segs(int32_t nbr, const int64_t *
         hv_cstart[P[4] + c] = (int32_t)(P[3] + c * HV_CHUNK);
         hv_crow[P[4] + c] = R;
     }
+}
+
+// A wave per row: its nonzero entries counted, then written (at[2 i]: first
+// entry of row i, at[2 i + 1]: rows with entries before it).
+template <int VB>
+__device__ __forceinline__ uint32_t dense_bits(const void *w, int64_t at)
+{
+    if constexpr (VB == 4) return ((const uint32_t *)w)[at];
+    else return ((const uint16_t *)w)[at];
+}
+template <int VB>
+__global__ __launch_bounds__(CTPB) void k_conv_rowcount(const void *w, int64_t ld, int32_t m, int32_t n, int32_t *cnt)
+{
+    const int lane = lane_id();
+    const int64_t i = (int64_t)blockIdx.x * (CTPB / WAVE) + (threadIdx.x >> 6);
+    if (i >= m) return;
+    int32_t c = 0;
+    for (int32_t j = lane; j < n; j += WAVE)
+        c += (dense_bits<VB>(w, i * ld + j) & (VB == 4 ? 0x7FFFFFFFu : 0x7FFFu)) ? 1 : 0;
+    c = wave_sum(c);
+    if (lane == 0) cnt[i] = c;
+}
+template <int VB>
+__global__ __launch_bounds__(CTPB) void k_conv_rowfill(const void *w, int64_t ld, int32_t m, int32_t n, const int32_t *at,
+                                                       uint32_t *col, uint8_t *val, int32_t *row, int32_t *chord)
+{
+    const int lane = lane_id();
+    const int64_t i = (int64_t)blockIdx.x * (CTPB / WAVE) + (threadIdx.x >> 6);
+    if (i >= m) return;
+    const int64_t p = at[i * 2];
+    const int32_t o = at[i * 2 + 1];
+    int64_t q = p;
+    for (int32_t j0 = 0; j0 < n; j0 += WAVE) {
+        const int32_t j = j0 + lane;
+        const uint32_t v = j < n ? dense_bits<VB>(w, i * ld + j) : 0u;
+        const bool nz = (v & (VB == 4 ? 0x7FFFFFFFu : 0x7FFFu)) != 0u;
+        const uint64_t b = ballot(nz);
+        if (nz) {
+            const int64_t e = q + __popcll(b & ((1ull << lane) - 1ull));
+            col[e] = (uint32_t)j | (e == p ? RE_START : 0u);
+            if constexpr (VB == 4) ((uint32_t *)val)[e] = v;
+            else ((uint16_t *)val)[e] = (uint16_t)v;
+        }
+        q += __popcll(b);
+    }
+    if (q == p) return;
+    if (lane == 0) row[o] = (int32_t)i;
+    for (int64_t c = p / RE_CHUNK + 1 + lane; c * RE_CHUNK <= q; c += WAVE) chord[c] = o;
 }
 
 // A thread per block column: its nonzero tiles.
@@ -391,6 +474,55 @@ struct Scratch {
     }
 };
 
+// The row-entry view (see DevMatrix), then the column-entry view: entries per
+// row, prefix sums on the host, the entries.
+template <int VB>
+dbs_status row_entries(int32_t m, int32_t n, const void *w, int64_t ld, int64_t nnz, hipStream_t s, dbs_matrix *A)
+{
+    Scratch tmp{s, {}};
+    DevMatrix &d = A->d;
+    const int64_t nchunk = (nnz + RE_CHUNK - 1) / RE_CHUNK;
+    int32_t *cnt = nullptr, *row = nullptr, *chord = nullptr;
+    uint32_t *col = nullptr;
+    uint8_t *val = nullptr;
+    CONV_TRY(hipMalloc((void **)&cnt, (size_t)m * 8 + 16), "hipMalloc (row counts)");
+    tmp.p.push_back(cnt);
+    const dim3 g((unsigned)((m + CTPB / WAVE - 1) / (CTPB / WAVE))), b(CTPB);
+    hipLaunchKernelGGL(k_conv_rowcount<VB>, g, b, 0, s, w, ld, m, n, cnt);
+    CONV_TRY(hipGetLastError(), "k_conv_rowcount");
+    // first entry and index among the nonempty rows, per row
+    std::vector<int32_t> h((size_t)m), at((size_t)m * 2);
+    CONV_TRY(hipMemcpyAsync(h.data(), cnt, (size_t)m * 4, hipMemcpyDeviceToHost, s), "hipMemcpy (row counts)");
+    CONV_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
+    int64_t p = 0, o = 0;
+    for (int32_t i = 0; i < m; ++i) {
+        at[(size_t)i * 2] = (int32_t)p;
+        at[(size_t)i * 2 + 1] = (int32_t)o;
+        p += h[(size_t)i];
+        o += h[(size_t)i] ? 1 : 0;
+    }
+    dbs_status st;
+    if ((st = conv_alloc(A->allocs, (size_t)nchunk * RE_CHUNK, &col, 0, s, 64)) != DBS_OK ||
+        (st = conv_alloc(A->allocs, (size_t)nnz * VB, &val, 0, s)) != DBS_OK ||
+        (st = conv_alloc(A->allocs, (size_t)o, &row, 0, s)) != DBS_OK ||
+        (st = conv_alloc(A->allocs, (size_t)nchunk + 1, &chord, 0xFF, s)) != DBS_OK)
+        return st;
+    CONV_TRY(hipMemcpyAsync(cnt, at.data(), at.size() * 4, hipMemcpyHostToDevice, s), "hipMemcpy (rows)");
+    hipLaunchKernelGGL(k_conv_rowfill<VB>, g, b, 0, s, w, ld, m, n, cnt, col, val, row, chord);
+    CONV_TRY(hipGetLastError(), "k_conv_rowfill");
+    CONV_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
+    d.re_col = col;
+    d.re_val = val;
+    d.re_row = row;
+    d.re_chord = chord;
+    d.re_nnz = (int32_t)nnz;
+    d.re_nchunk = (int32_t)nchunk;
+    d.re_sparse = true;
+    d.m = m;
+    d.n = n;
+    return column_entries(A);
+}
+
 template <int VB>
 dbs_status convert(int32_t m, int32_t n, const void *d_w, int64_t ld, const dbs_build_opts &o, hipStream_t s,
                    dbs_matrix *A)
@@ -429,6 +561,7 @@ dbs_status convert(int32_t m, int32_t n, const void *d_w, int64_t ld, const dbs_
         CONV_TRY(hipMemcpyAsync(rs.data(), rstat, rs.size() * 8, hipMemcpyDeviceToHost, s), "hipMemcpy (rows)");
         CONV_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
     }
+    int64_t coo = 0;  // entries in COO blocks
     int64_t nnz = 0, by_type[DBS_NUM_BLOCK_TYPES] = {0, 0, 0, 0, 0};
     for (int32_t R = 0; R < nbr; ++R) {
         const int64_t *x = rs.data() + (size_t)R * RS;
@@ -439,6 +572,7 @@ dbs_status convert(int32_t m, int32_t n, const void *d_w, int64_t ld, const dbs_
         q[3] = p[3] + x[3];
         q[4] = p[4] + (x[3] + HV_CHUNK - 1) / HV_CHUNK;
         nnz += x[4];
+        coo += x[10];
         for (int t = 0; t < DBS_NUM_BLOCK_TYPES; ++t) by_type[t] += x[5 + t];
     }
     const int64_t *tot = pre.data() + (size_t)nbr * PRE;
@@ -467,13 +601,23 @@ dbs_status convert(int32_t m, int32_t n, const void *d_w, int64_t ld, const dbs_
         (st = conv_alloc(A->allocs, (size_t)nchunk + 1, &hv_cstart, 0, s)) != DBS_OK ||
         (st = conv_alloc(A->allocs, (size_t)nchunk, &hv_crow, 0, s)) != DBS_OK ||
         (st = conv_alloc(A->allocs, (size_t)std::max<int64_t>(nbr, 1), &hv_rowchunks, 0, s)) != DBS_OK ||
-        (st = conv_alloc(A->allocs, (size_t)bytes, &pay, 0, s, 16)) != DBS_OK)
+        (st = conv_alloc(A->allocs, (size_t)bytes, &pay, 0, s, PAYLOAD_PAD)) != DBS_OK)
         return st;
     CONV_TRY(scratch((size_t)nblk * 8, (void **)&blk_desc), "hipMalloc (descriptors)");
+    const bool list = nblk > 0 && nnz >= BLOCK_LIST_ENTRIES * nblk;
+    int32_t *ab_col = nullptr, *ab_rptr = nullptr, *blk_col = nullptr;
+    uint64_t *ab_desc = nullptr;
+    if (list) {
+        if ((st = conv_alloc(A->allocs, (size_t)nblk, &ab_col, 0, s)) != DBS_OK ||
+            (st = conv_alloc(A->allocs, (size_t)nblk, &ab_desc, 0, s)) != DBS_OK ||
+            (st = conv_alloc(A->allocs, (size_t)nbr * MC_COUNT + 1, &ab_rptr, 0, s)) != DBS_OK)
+            return st;
+        CONV_TRY(scratch((size_t)nblk * 4, (void **)&blk_col), "hipMalloc (block columns)");
+    }
     int32_t *ccnt = nullptr;
     CONV_TRY(scratch((size_t)nbc * 4, (void **)&ccnt), "hipMalloc (column counts)");
     if (nblk > 0) {
-        ConvOut out{pay, sl_col, sl_desc, hv_col, hv_desc, blk_desc};
+        ConvOut out{pay, sl_col, sl_desc, hv_col, hv_desc, blk_desc, blk_col};
         hipLaunchKernelGGL(k_conv_write<VB>, dim3((unsigned)tgrid), dim3(CTPB), 0, s, d_w, ld, m, n, nbc, ntiles,
                            tinfo, toff, tb, tseg, thv, pre_d, out);
         CONV_TRY(hipGetLastError(), "k_conv_write");
@@ -485,6 +629,11 @@ dbs_status convert(int32_t m, int32_t n, const void *d_w, int64_t ld, const dbs_
                                nchunk, hv_crow, hv_rowchunks);
             CONV_TRY(hipGetLastError(), "k_conv_rowchunks");
         }
+    }
+    if (list) {
+        hipLaunchKernelGGL(k_conv_list, dim3((unsigned)((nbr + CTPB / WAVE - 1) / (CTPB / WAVE))), dim3(CTPB), 0, s, nbr,
+                           pre_d, blk_col, blk_desc, ab_col, ab_desc, ab_rptr);
+        CONV_TRY(hipGetLastError(), "k_conv_list");
     }
     const int32_t nheavy32 = (int32_t)nheavy;
     CONV_TRY(hipMemcpyAsync(hv_cstart + nchunk, &nheavy32, 4, hipMemcpyHostToDevice, s), "hipMemcpy (chunks)");
@@ -525,6 +674,13 @@ dbs_status convert(int32_t m, int32_t n, const void *d_w, int64_t ld, const dbs_
     d.hv_cstart = hv_cstart;
     d.hv_crow = hv_crow;
     d.hv_rowchunks = hv_rowchunks;
+    if (entries_wanted(nnz, entries_sparse(nnz, coo, o.force_type), d.dtype, o.force_type)) {
+        const dbs_status es = row_entries<VB>(m, n, d_w, ld, nnz, s, A);
+        if (es != DBS_OK) return es;
+    }
+    d.ab_col = ab_col;
+    d.ab_desc = ab_desc;
+    d.ab_rptr = ab_rptr;
     d.nheavy = nheavy;
     d.nchunk = nchunk;
     d.pay = pay;

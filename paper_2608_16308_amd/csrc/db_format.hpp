@@ -116,6 +116,19 @@ DBS_HD uint32_t record_align(uint32_t type, uint32_t vbytes)
     return type == T_COO ? (vbytes > 1 ? vbytes : 1u) : 16u;
 }
 
+// Classes of the block list that the matrix-core pass walks, in its order
+// within a block row: Dense blocks; ForceCSR and patched-CSR blocks of at most
+// MC_RUN entries; COO blocks of at most 64; the others.
+enum : int { MC_DENSE = 0, MC_ROWS = 1, MC_COO = 2, MC_OTHER = 3, MC_COUNT = 4 };
+constexpr uint32_t MC_RUN = 128;
+DBS_HD int mfma_class(uint32_t type, uint32_t nnz)
+{
+    if (type == T_DENSE) return MC_DENSE;
+    if ((type == T_FCSR || type == T_CSR) && nnz <= MC_RUN) return MC_ROWS;
+    if (type == T_COO && nnz <= 64u) return MC_COO;
+    return MC_OTHER;
+}
+
 // Entries per chunk of the row-entry view: whole wave steps of 64, and the
 // grain at which its rows can be found.
 constexpr int32_t RE_CHUNK = 256;

@@ -13,6 +13,10 @@ constexpr int WAVE = 64;
 
 __device__ __forceinline__ int lane_id() { return (int)__lane_id(); }
 
+// The wave's number in its workgroup, known to be the same for all its lanes
+// (so that what follows from it stays in scalar registers and branches).
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
+
 __device__ __forceinline__ uint64_t ballot(bool p) { return (uint64_t)__ballot(p ? 1 : 0); }
 
 __device__ __forceinline__ int ctz32(uint32_t v) { return __builtin_ctz(v); }

@@ -63,7 +63,7 @@ __global__ __launch_bounds__(ES_TPB) void k_entry_scatter(const int32_t *__restr
     __shared__ uint64_t s_tot[ES_TPB / WAVE];
     __shared__ uint64_t s_base;
     const int32_t t = blockIdx.x * ES_TPB + threadIdx.x;
-    const int lane = lane_id(), wv = threadIdx.x >> 6;
+    const int lane = lane_id(), wv = wave_id();
     int32_t j = -1;
     uint32_t x = 0;
     if (t < k) {
@@ -187,7 +187,7 @@ constexpr int EPUSH_TPB = 256;
 template <int MODE>
 __global__ __launch_bounds__(EPUSH_TPB) void k_entry_push(EntryPushArgs a)
 {
-    entry_push<MODE>(a, (int64_t)blockIdx.x * (EPUSH_TPB / WAVE) + (threadIdx.x >> 6),
+    entry_push<MODE>(a, (int64_t)blockIdx.x * (EPUSH_TPB / WAVE) + wave_id(),
                      (int64_t)gridDim.x * (EPUSH_TPB / WAVE));
 }
 
@@ -229,7 +229,7 @@ struct EntryPullArgs {
     const uint32_t *omask;
     int32_t complement;
     double *yacc;
-    uint32_t *ybits;
+    uint32_t *ybits;  // NULL: dense output
     int32_t *counters;
     int32_t scanned;  // a scan ran: its choice decides whether there is work
     // open choice (DECIDE): the selector's numbers and the push side
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(EP_TPB) void k_entry_pull(EntryPullArgs a)
     __shared__ uint32_t q_col[EP_WAVES][EP_QUEUE], q_ent[EP_WAVES][VAL ? EP_QUEUE : 1];
     __shared__ uint32_t q_ord[EP_WAVES][EP_QUEUE];
     __shared__ uint32_t s_cnt[EP_WAVES * 2];
-    const int t = threadIdx.x, lane = lane_id(), wv = t >> 6;
+    const int t = threadIdx.x, lane = lane_id(), wv = wave_id();
     // the wave's chunks; its first words go out before the bitmap is formed
     const int64_t W = (int64_t)gridDim.x * EP_WAVES, wid = (int64_t)wv * gridDim.x + blockIdx.x;
     const int32_t c0 = (int32_t)(wid * a.nchunk / W), c1 = (int32_t)((wid + 1) * a.nchunk / W);
@@ -383,6 +383,11 @@ __global__ __launch_bounds__(EP_TPB) void k_entry_pull(EntryPullArgs a)
             }
         }
     };
+    // y structure (none for a dense output: atomics on one line take turns at
+    // about 8 ns, and 5003 rows of 350 entries share few lines -- 27 us with
+    // them, 10 without; testing the word before the atomic tripled the time of
+    // a Boolean step on R-MAT 18)
+    auto mark = [&](int32_t w, uint32_t bits) { atomicOr(&a.ybits[w], bits); };
     // the first n queued hits
     auto flush = [&](uint32_t n) {
         const bool on = (uint32_t)lane < n;
@@ -414,7 +419,7 @@ __global__ __launch_bounds__(EP_TPB) void k_entry_pull(EntryPullArgs a)
             }
         } else if (run_ok) {
             put(lane == 0, run, run_row, run_sum, false);
-            if (lane == 0) atomicOr(&a.ybits[run_row >> 5], 1u << (run_row & 31));
+            if (a.ybits && lane == 0) mark(run_row >> 5, 1u << (run_row & 31));
         }
         seg_step<dppc::ROW_SHR + 1>(sum, ok, o);
         seg_step<dppc::ROW_SHR + 2>(sum, ok, o);
@@ -429,7 +434,7 @@ __global__ __launch_bounds__(EP_TPB) void k_entry_pull(EntryPullArgs a)
         const uint32_t key = on ? (uint32_t)(row >> 5) : 0xFFFFFFFFu;
         const uint32_t bits = wave_run_or(end && ok ? 1u << (row & 31) : 0u, key);
         const uint32_t nkey = dpp_mov<dppc::WF_SL1>(~key, key);
-        if (on && bits && nkey != key) atomicOr(&a.ybits[key], bits);
+        if (a.ybits && on && bits && nkey != key) mark((int32_t)key, bits);
         const int last = (int)n - 1;
         run = readlane_u32(o, last);
         run_row = (int32_t)readlane_u32((uint32_t)row, last);
@@ -477,7 +482,7 @@ __global__ __launch_bounds__(EP_TPB) void k_entry_pull(EntryPullArgs a)
     if (run != NONE && run_ok) {
         // the next share may go on with this row
         put(lane == 0, run, run_row, run_sum, true);
-        if (lane == 0) atomicOr(&a.ybits[run_row >> 5], 1u << (run_row & 31));
+        if (a.ybits && lane == 0) mark(run_row >> 5, 1u << (run_row & 31));
     }
 }
 
@@ -555,10 +560,11 @@ static EntryPullArgs pull_args(const DevMatrix &A, const DevCtx &C, const uint32
 }
 
 hipError_t launch_entry_pull(const DevMatrix &A, const DevCtx &C, int mode, const uint32_t *omask, int complement,
-                             bool scanned, hipStream_t s)
+                             bool scanned, bool dense_out, hipStream_t s)
 {
     EntryPullArgs a = pull_args(A, C, omask, complement);
     a.scanned = scanned ? 1 : 0;
+    if (dense_out) a.ybits = nullptr;
     switch (mode) {
     case M_F32: return entry_pull<M_F32, false>(a, s);
     case M_F16: return entry_pull<M_F16, false>(a, s);
@@ -627,7 +633,7 @@ __global__ __launch_bounds__(256) void k_ce_fill(const uint32_t *__restrict__ co
 {
     const int lane = lane_id();
     const uint64_t upto = lane == WAVE - 1 ? ~0ull : (1ull << (lane + 1)) - 1ull;
-    for (int32_t c = blockIdx.x * 4 + (threadIdx.x >> 6); c < nchunk; c += gridDim.x * 4) {
+    for (int32_t c = blockIdx.x * 4 + wave_id(); c < nchunk; c += gridDim.x * 4) {
         int32_t ord = chord[c];
         for (int j = 0; j < RE_CHUNK / WAVE; ++j) {
             const int64_t e = (int64_t)c * RE_CHUNK + j * WAVE + lane;

@@ -2744,6 +2744,7 @@ __global__ __launch_bounds__(TPB) void k_finalize_dense(double *__restrict__ yac
 {
     const int64_t stride = (int64_t)gridDim.x * TPB;
     for (int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x; i < m; i += stride) {
+        if (!y) break;  // (only the masks and the densified x to restore)
         double v = yacc[i];
         if constexpr (MODE == M_F32) ((float *)y)[i] = (float)v;
         else ((uint16_t *)y)[i] = f64_to_f16_rne(v);

@@ -48,6 +48,15 @@ struct DevMatrix {
     // no edge leads to them, and the pull levels then skip whole block rows
     // sooner.
     const uint32_t *row_occ = nullptr;
+    // Block list (valued matrices whose blocks hold at least
+    // BLOCK_LIST_ENTRIES entries on average; ab_col NULL for others): every
+    // block, by block row, within it by class (mfma_class), within that by
+    // block column -- block column, descriptor, and where class k of block
+    // row R begins at [MC_COUNT R + k] (MC_COUNT nbr + 1).  The matrix-core
+    // pass for dense activations walks it.
+    const int32_t *ab_col = nullptr;
+    const uint64_t *ab_desc = nullptr;
+    const int32_t *ab_rptr = nullptr;
     // Row-entry view (re_nchunk = 0: the matrix has none): every entry in row
     // order with ascending columns -- the column word (bit 31: first entry of
     // its row) and the value -- padded to whole chunks of RE_CHUNK entries;
@@ -73,6 +82,13 @@ struct DevMatrix {
     // (m + 1; a row without entries repeats the next row's first entry).
     const int2 *re_info = nullptr;
 };
+
+// Below this many entries per block the block walk of k_rows_mfma (about 70
+// vector instructions a block) costs more than the pull over slots or entries.
+constexpr int64_t BLOCK_LIST_ENTRIES = 8;
+// Zeroed bytes behind the payload: a whole value run (MC_RUN fp32 values) read
+// from the last record stays inside the allocation.
+constexpr size_t PAYLOAD_PAD = 512;
 
 // Push work items and tasks share a 64-bit count: tasks in the low bits.
 constexpr int EV_TASK_BITS = 32;
@@ -227,13 +243,14 @@ hipError_t launch_main(const DevMatrix &A, const DevCtx &C, int mode, const void
 //   launch_entry_scatter  blocker that also lists push items (into C.items:
 //                         at most one per x index), as push and auto need
 //   launch_entry_pull     pull; scanned: a scan ran, and the kernel returns
-//                         at once when its choice is push
+//                         at once when its choice is push; dense_out: the y
+//                         structure is not wanted
 //   launch_entry_push     push
 //   launch_entry_auto     the choice is taken on the device
 hipError_t launch_entry_scatter(const DevMatrix &A, const DevCtx &C, int mode, int32_t k, const int32_t *x_idx,
                                 const void *x_val, hipStream_t s);
 hipError_t launch_entry_pull(const DevMatrix &A, const DevCtx &C, int mode, const uint32_t *omask, int complement,
-                             bool scanned, hipStream_t s);
+                             bool scanned, bool dense_out, hipStream_t s);
 hipError_t launch_entry_push(const DevMatrix &A, const DevCtx &C, int mode, const uint32_t *omask, int complement,
                              hipStream_t s);
 hipError_t launch_entry_auto(const DevMatrix &A, const DevCtx &C, int mode, const uint32_t *omask, int complement,
@@ -255,6 +272,14 @@ hipError_t launch_finalize_dense(const DevMatrix &A, const DevCtx &C, int mode, 
 bool rows_dx_fits(const DevMatrix &A, const void *x_dense);
 hipError_t launch_rows_dx(const DevMatrix &A, const DevCtx &C, int mode, const void *x_dense, void *y,
                           float *y32, hipStream_t s);
+// Dense activations (1 <= nb <= 8, rows of x) on a matrix with a block list
+// (rows_mfma_fits), in one kernel on the matrix cores.  With rows_mfma_parts
+// > 1 it sums through yacc (nb sets of 16 nbr accumulators, zero between
+// calls) and the context's block-row counts; else it touches no scratch.
+bool rows_mfma_fits(const DevMatrix &A);
+int32_t rows_mfma_parts(const DevMatrix &A);
+hipError_t launch_rows_mfma(const DevMatrix &A, const DevCtx &C, double *yacc, int32_t nb, const void *x, void *y,
+                            float *y32, hipStream_t s);
 // Batched dense activations (NB in {2, 4, 8} vectors per pass, nb <= NB of
 // them real): the padded copies into xdb (NB * 16 nbc entries) and their
 // union mask; the pull over a matrix without COO blocks into yaccb (NB * 16

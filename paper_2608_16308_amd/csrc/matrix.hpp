@@ -11,3 +11,7 @@ struct dbs_matrix {
     dbs_matrix_info info{};
     std::vector<void *> allocs;  // device allocations owned by the matrix
 };
+
+// Adds the column-entry view of a matrix that has its row-entry view (on the
+// default stream; returns when done).
+dbs_status column_entries(dbs_matrix *A);

@@ -132,3 +132,33 @@ def test_repeated_indices_count_once(torch, k):
         assert st["n_nzblk"] == np.unique(xi >> 4).size
         assert np.array_equal(y_idx.cpu().numpy(), ri)
         assert oracle.within_tol(y_val.cpu().numpy(), rv, rs, REL_TOL).all()
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("m,n,keep", [(16, 16, 0.004), (37, 1500, 0.02), (1000, 129, 0.03), (513, 4099, 0.02),
+                                      (40, 16400, 0.05)])
+def test_views_of_a_device_built_matrix(torch, dtype, m, n, keep):
+    """The device construction counts and fills the same views: sparse and
+    dense x on both paths, with empty rows, against the oracle."""
+    rng = wl.rng_for(wl.W_RAND, 99, m, n)
+    w = np.where(rng.random((m, n)) < keep, rng.uniform(0.1, 1.0, (m, n)), 0.0).astype(dtype)
+    w[m // 3:m // 2] = 0
+    w[m - 1, n - 1] = 0.5
+    r, c = np.nonzero(w)
+    a = wl.csr_from_coo(m, n, r, c, w[r, c])
+    A, om = dbs.Matrix.from_dense(to_dev(w)), oracle_matrix(a)
+    ctx = dbs.Context(A)
+    for k in (1, 7, n // 8 + 1, n):
+        xi, xv = x_of(n, k, 7, dtype)
+        for p in ("push", "pull", "auto"):
+            log(f"device-built {dtype.__name__} {m}x{n} k={k} path={p}")
+            check_spmspv(ctx, A, om, a, xi, xv.astype(np.float64), path=p, label=f"device-built {m}x{n} k={k} {p}")
+        x = np.zeros(n, dtype)
+        x[xi] = xv
+        y32 = torch.empty(m, dtype=torch.float32, device="cuda:0")
+        ctx.spmspv_dense(A, to_dev(x), y32=y32)
+        torch.cuda.synchronize()
+        ri, rv, rs = om.spmspv(xi, xv.astype(np.float64))
+        y64, S = np.zeros(m), np.zeros(m)
+        y64[ri], S[ri] = rv, rs
+        assert oracle.within_tol(y32.cpu().numpy(), y64, S, REL_TOL).all()

@@ -1,0 +1,151 @@
+"""GPU parity of the matrix-core pass for dense activations (one to eight)
+against the oracle: every block class (Dense, row formats, COO in the
+descriptor and in a record, ForceCSC, row formats of more than 128 entries),
+ragged shapes, one workgroup and several per block row (block rows of more
+than 128 blocks), infinities and NaN in A and x, fp16 subnormals.
+
+fp16 outputs within one ulp of the fp64 sum's rounding; fp32 within the
+suite's 1e-5 * sum |a_ij x_j| (a block's 16 products are summed in fp32, the
+blocks in fp64)."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2608_16308_amd as dbs
+import workloads as wl
+from gpu_helpers import REL_TOL, check_f16, gpu_matrix, log, oracle_matrix, to_dev, torch_mod
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    t = torch_mod()
+    if not t.cuda.is_available():
+        pytest.skip("no GPU")
+    return t
+
+
+def check(ctx, A, om, X, label):
+    """Y = A X for the rows of X, through the batched and the one-vector call."""
+    torch = torch_mod()
+    log(label)
+    nb = X.shape[0]
+    refs = [oracle_sums(om, X[b]) for b in range(nb)]
+    for rep in range(2):  # (the second finds what the first left in the scratch)
+        Y32 = torch.full((nb, om.m), -7.0, dtype=torch.float32, device="cuda:0")
+        if nb == 1:
+            y, st = ctx.spmspv_dense(A, to_dev(X[0]), y32=Y32[0], stats=True)
+            Y = y[None]
+        else:
+            Y, st = ctx.spmm_dense(A, to_dev(X), Y32=Y32, stats=True)
+        torch.cuda.synchronize()
+        blocks = np.unique(np.nonzero((X != 0).any(0))[0] >> 4)
+        assert st["n_nzblk"] == blocks.size, (label, st)
+        for b in range(nb):
+            y64, S = refs[b]
+            g, g32 = Y[b].cpu().numpy(), Y32[b].cpu().numpy()
+            if X.dtype == np.float16:
+                check_f16(g, y64, f"{label} vector {b}")
+            else:
+                assert oracle.within_tol(g, y64, S, REL_TOL).all(), f"{label} vector {b}"
+            assert oracle.within_tol(g32, y64, S, REL_TOL).all(), f"{label} vector {b} fp32 sums"
+
+
+def oracle_sums(om, x):
+    idx = np.nonzero(x != 0)[0].astype(np.int32)   # (NaN counts as active)
+    ri, rv, rs = om.spmspv(idx, x[idx].astype(np.float64))
+    y64, S = np.zeros(om.m), np.zeros(om.m)
+    y64[ri], S[ri] = rv, rs
+    return y64, S
+
+
+def activations(nb, n, dtype, key, density=0.3):
+    rng = wl.rng_for(wl.W_RAND, 120, key)
+    X = np.where(rng.random((nb, n)) < density, rng.uniform(-1, 1, (nb, n)), 0.0).astype(dtype)
+    X[0, : n // 3] = 0  # whole inactive vector blocks
+    if nb > 2:
+        X[1] = 0
+    return X
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("force", [-1, 0, 1, 2, 3, 4])
+def test_block_classes(torch, dtype, force):
+    rng = wl.rng_for(wl.W_RAND, 121, force + 1)
+    m, n = 90, 200
+    # blocks from a few entries to full, column- and row-skewed ones among them
+    p = np.kron(rng.choice([0.02, 0.1, 0.3, 0.6, 1.0], (6, 13)), np.ones((16, 16)))[:m, :n]
+    keep = rng.random((m, n)) < p
+    keep[16:32, 32:48] = False
+    keep[16:32, [33, 40, 41]] = True          # column skew
+    keep[32:48, 48:64] = False
+    keep[[33, 40, 41], 48:64] = True          # row skew
+    keep[48:64, 64:80] = False
+    keep[50, 70] = True                       # one entry
+    r, c = np.nonzero(keep)
+    a = wl.csr_from_coo(m, n, r, c, wl._nonzero_uniform(rng, -1.0, 1.0, r.size, dtype=dtype))
+    opts = dbs.default_opts(force_type=force, th1=250 if force == 4 else 128)
+    A, om = gpu_matrix(a, opts), oracle_matrix(a)
+    ctx = dbs.Context(A)
+    for nb in (1, 2, 3, 8):
+        check(ctx, A, om, activations(nb, n, dtype, nb), f"classes {dtype.__name__} force={force} nb={nb}")
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("m,n,keep", [(16, 2048, 0.5), (33, 4100, 0.4), (700, 3000, 0.1), (4096, 2100, 0.06),
+                                      (17, 16, 0.5), (3290, 2064, 0.3)])
+def test_shapes(torch, dtype, m, n, keep):
+    """One block row in many parts, a few, the 16-wave shape (256 block rows),
+    short rows, ragged both ways."""
+    rng = wl.rng_for(wl.W_RAND, 122, m, n)
+    mask = rng.random((m, n)) < keep
+    mask[16:32] &= n > 100                     # a block row without blocks in the narrow case
+    r, c = np.nonzero(mask)
+    a = wl.csr_from_coo(m, n, r, c, wl._nonzero_uniform(rng, -1.0, 1.0, r.size, dtype=dtype))
+    A, om = gpu_matrix(a), oracle_matrix(a)
+    ctx = dbs.Context(A)
+    for nb in (1, 5):
+        check(ctx, A, om, activations(nb, n, dtype, 10 + nb, 0.2), f"{dtype.__name__} {m}x{n} keep={keep} nb={nb}")
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+def test_not_finite(torch, dtype):
+    """Infinities and NaN reach the rows that hold the entry, and no others:
+    not a row without the entry, not a token whose x is inactive there."""
+    rng = wl.rng_for(wl.W_RAND, 123, 0)
+    m, n = 70, 150
+    r, c = np.nonzero(rng.random((m, n)) < 0.4)
+    v = wl._nonzero_uniform(rng, -1.0, 1.0, r.size, dtype=dtype)
+    a = wl.csr_from_coo(m, n, r, c, v)
+    X = activations(4, n, dtype, 20, 0.5)
+    X[2, 40:44] = [np.inf, 0.0, np.nan, -np.inf]
+    for what in ("x", "A"):
+        if what == "A":
+            X = activations(4, n, dtype, 21, 0.5)
+            a.vals[[5, 900, 2000]] = [np.inf, np.nan, -np.inf]
+        A, om = gpu_matrix(a), oracle_matrix(a)
+        ctx = dbs.Context(A)
+        Y32 = torch.empty((4, m), dtype=torch.float32, device="cuda:0")
+        ctx.spmm_dense(A, to_dev(X), Y32=Y32)
+        torch.cuda.synchronize()
+        for b in range(4):
+            y64, _ = oracle_sums(om, X[b])
+            g = Y32[b].cpu().numpy()
+            log(f"not finite in {what}, vector {b}: {np.sum(~np.isfinite(y64))} rows")
+            assert np.array_equal(np.isnan(g), np.isnan(y64))
+            assert np.array_equal(np.isinf(g), np.isinf(y64)) and np.array_equal(g[np.isinf(g)], y64[np.isinf(y64)])
+            ok = np.isfinite(y64)
+            assert np.allclose(g[ok], y64[ok], rtol=0, atol=1e-5 * n)
+
+
+def test_fp16_subnormals(torch):
+    rng = wl.rng_for(wl.W_RAND, 124, 0)
+    m, n = 64, 128
+    r, c = np.nonzero(rng.random((m, n)) < 0.5)
+    v = (rng.integers(1, 1024, r.size) * 2.0 ** -24).astype(np.float16)      # subnormal weights
+    a = wl.csr_from_coo(m, n, r, c, v)
+    A, om = gpu_matrix(a), oracle_matrix(a)
+    X = np.where(rng.random((3, n)) < 0.5, rng.uniform(1, 100, (3, n)), 0).astype(np.float16)
+    X[1] = (rng.integers(0, 1024, n) * 2.0 ** -24).astype(np.float16)         # and a subnormal activation
+    check(dbs.Context(A), A, om, X, "fp16 subnormals")
