@@ -685,7 +685,13 @@ hipError_t launch_bfs_level(const DevMatrix &A, const DevBfs &B, int32_t l, int3
     const BfsArgs a = bfs_args(A, B, level, parent, policy, th3, push_share);
     const int64_t want = std::max<int64_t>(((int64_t)A.n + BL_TPB - 1) / BL_TPB,
                                            ((int64_t)A.re_nnz + 8 * BL_TPB - 1) / (8 * BL_TPB));
-    const dim3 g((uint32_t)std::min<int64_t>(want, 512)), b(BL_TPB);
+    // Where every wave has rows to take (four per lane and turn) one workgroup
+    // per compute unit: with two, more of them queue at the counters where
+    // items are reserved (R-MAT 22 165 against 180 us).  Smaller graphs take
+    // two: a stencil of 207,360 rows takes 980 us from one source and 1078
+    // from another, with one workgroup each 1010 and 1031.
+    const bool four = A.n >= 4 * WAVE * (BL_WAVES * 256);
+    const dim3 g((uint32_t)std::min<int64_t>(want, four ? 256 : 512)), b(BL_TPB);
     if (a.th3n > 0.0 && policy == 0 && l > 0) {
         hipLaunchKernelGGL(k_bfs_list, g, b, 0, s, a, l);
         hipLaunchKernelGGL(k_bfs_list_done, dim3(1), dim3(1), 0, s, a, l);
@@ -695,7 +701,7 @@ hipError_t launch_bfs_level(const DevMatrix &A, const DevBfs &B, int32_t l, int3
         while (((int64_t)A.n >> fold) >= (int64_t)BS_BITMAP_WORDS * 32) ++fold;
         hipLaunchKernelGGL(k_bfs_stream, dim3((uint32_t)std::min<int32_t>(A.re_nchunk, 512)), b, 0, s, a, l, fold);
     }
-    if (A.n >= 4 * WAVE * (BL_WAVES * 256)) hipLaunchKernelGGL(k_bfs_level<4>, g, b, 0, s, a, l);
+    if (four) hipLaunchKernelGGL(k_bfs_level<4>, g, b, 0, s, a, l);
     else hipLaunchKernelGGL(k_bfs_level<1>, g, b, 0, s, a, l);
     return hipGetLastError();
 }
