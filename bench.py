@@ -47,7 +47,7 @@ def log(*a):
 def kernel_sources_digest() -> str:
     import hashlib
     h = hashlib.sha256()
-    for f in ("kernels.hip", "device_common.hpp", "db_format.hpp", "kernels.hpp"):
+    for f in ("kernels.hip", "entries.hip", "bfs.hip", "decode.hip", "device_common.hpp", "db_format.hpp", "kernels.hpp"):
         with open(os.path.join(ROOT, "paper_2608_16308_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -778,8 +778,8 @@ def main():
         hm_gteps = len(gteps) / sum(1.0 / x for x in gteps)
         log(f"[bench] BFS: harmonic mean {hm_gteps:.2f} GTEPS over {len(srcs)} sources; {per_src[:3]}")
         result["bfs"] = {"workload": f"rmat{args.bfs_scale}_bfs_{len(srcs)}_sources", "gteps_hmean": round(hm_gteps, 3),
-                         "selector": "per level push iff the push tasks (blocks in the block-CSC lists of the "
-                                     "frontier's column blocks) < 0.1 nblk",
+                         "selector": "per level push iff the frontier's columns hold < 2% of the entries, or < 10%, "
+                                     "fewer than the unreached vertices' and < 4 times the level before",
                          "gteps_min": round(min(gteps), 3), "gteps_max": round(max(gteps), 3),
                          "ms_mean": round(1e3 * float(np.mean(times)), 3), "db_build_s": round(gbuild, 2),
                          "edges_counted": "undirected edges of the source's component", "per_source": per_src}

@@ -373,8 +373,10 @@ dbs_status dbs_spmspv_noalloc(const dbs_matrix *A, dbs_semiring sr, int32_t x_nn
  * (Sec. 4.1).  d_y_dense receives all m outputs in A's dtype (rows with no
  * active product are 0), rounded to nearest even from the fp64 sum.
  * d_y_f32 (NULL allowed) receives the same sums rounded to fp32.
- * path AUTO with th3 <= 0 on a matrix without COO blocks takes pull (see
- * DBS_TH3_DEFAULT); th3 > 0 applies the paper's rule on the device.
+ * With AUTO and th3 <= 0, or with pull, no selector runs: the entries are
+ * streamed (most of them in COO blocks) or all blocks multiplied (eight
+ * entries per block and more); stats then reports what the selector would
+ * have counted and chosen.  th3 > 0 applies the paper's rule on the device.
  * F32 and F16 matrices only.                                               */
 dbs_status dbs_spmspv_dense(dbs_ctx *ctx, const dbs_matrix *A, const void *d_x_dense,
                             dbs_path path, float th3, void *d_y_dense, float *d_y_f32,
@@ -387,14 +389,15 @@ dbs_status dbs_spmspv_dense(dbs_ctx *ctx, const dbs_matrix *A, const void *d_x_d
  *   d_y        nb x m outputs, row-major, A's dtype, rounded to nearest even
  *              from the fp64 sums; d_y_f32 (NULL allowed) nb x m fp32 sums
  *   nb         1 .. DBS_MAX_BATCH
- * For a matrix without COO blocks (every block Dense / ForceCSR / ForceCSC /
- * patched CSR, the regime of pruned decode layers) the nb vectors share one
- * pull pass: the blocks active for any vector are visited once and every
- * stored value is loaded once for all of them (the path is pull; N_nzblk in
- * stats counts the union of the vectors' vector blocks).  Otherwise, or for
- * nb = 1, the vectors are taken one dbs_spmspv_dense call each.  The first
- * batched call allocates DBS_MAX_BATCH padded x copies and fp64 accumulator
- * sets for the context's largest shape (kept until dbs_ctx_destroy).        */
+ * For a matrix of eight entries per block and more the nb vectors share one
+ * pass over the blocks on the matrix cores (path reports pull; N_nzblk in
+ * stats counts the union of the vectors' vector blocks).  Two fp32 vectors on
+ * a matrix of 256 block rows and more without COO blocks share a pass with a
+ * lane per row.  Otherwise, or for nb = 1, the vectors are taken one
+ * dbs_spmspv_dense call each.  A call that needs them (statistics, the
+ * lane-per-row pass, block rows taken in parts)
+ * allocates, once, DBS_MAX_BATCH padded x copies and fp64 accumulator sets
+ * for the context's largest shape (kept until dbs_ctx_destroy).             */
 #define DBS_MAX_BATCH 8
 dbs_status dbs_spmm_dense(dbs_ctx *ctx, const dbs_matrix *A, int32_t nb, const void *d_x, void *d_y,
                           float *d_y_f32, dbs_call_stats *stats);
@@ -415,11 +418,14 @@ typedef struct {
  * Edge u -> v iff A[v][u] is stored; A must be square.  A matrix built
  * from CSR on the host also carries which rows hold entries: BFS counts the
  * others as visited from the start (no edge reaches them), so that pull
- * levels skip their block rows sooner; the results are the same.
+ * levels skip their block rows sooner; the results are the same.  A matrix
+ * that carries entry views (DBS_BFS_PUSH_ENTRIES) runs one kernel per level
+ * over them, bottom-up rows ending at their first parent.
  *   d_level[n]   level of each vertex, -1 if unreachable, level[source] = 0
  *   d_parent[n]  smallest-id vertex of the previous level with an edge to v;
  *                parent[source] = source; -1 if unreachable
- * The host reads one small counter per level to detect termination.
+ * Levels are launched ahead of their results (the kernels after the last one
+ * return at once); the host reads one record per batch of launches.
  * stats (NULL allowed) is filled on return.                                */
 dbs_status dbs_bfs(dbs_ctx *ctx, const dbs_matrix *A, int32_t source, int32_t *d_level,
                    int32_t *d_parent, dbs_path policy, float th3, dbs_bfs_stats *stats);

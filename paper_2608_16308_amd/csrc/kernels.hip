@@ -1,6 +1,9 @@
 // gfx950 kernels of the dual-view blocked SpMSpV (DB-SpMSpV).
 //
-// One call of y = A x runs these kernels on the context's stream:
+// Matrices of short COO blocks run over entry views (entries.hip), BFS on them
+// one kernel per level (bfs.hip), dense activations on the matrix cores
+// (decode.hip).  Every other call of y = A x -- matrices of filled blocks,
+// forced block formats -- runs these kernels on the context's stream:
 //   k_scatter / k_ballot  vector blocker (Sec. 3.2.2, 4.1): dense x values and
 //                         the 16-bit blk_x_mask of every 16-element vector block
 //   k_scan                single-pass look-back scan over vector blocks: the
