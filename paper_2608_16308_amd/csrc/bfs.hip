@@ -27,6 +27,7 @@
 
 #include "device_common.hpp"
 #include "kernels.hpp"
+#include "turn_queue.hpp"
 
 namespace dbs {
 
@@ -75,6 +76,13 @@ struct BfsLds {
     uint64_t tot[BL_WAVES];
     uint64_t base, ent;
     uint32_t nq, found, inc, nvb;
+};
+
+// The push queue of a workgroup (queue_is_full).
+struct BfsQueueOps {
+    BfsLds &L;
+    __device__ __forceinline__ void barrier() { __syncthreads(); }
+    __device__ __forceinline__ uint32_t count() { return L.nq; }
 };
 
 __device__ __forceinline__ bool bit_of(const uint32_t *b, uint32_t i) { return (b[i >> 5] >> (i & 31)) & 1u; }
@@ -177,14 +185,21 @@ __global__ __launch_bounds__(BL_TPB, 8) void k_bfs_level(BfsArgs a, int32_t l)
     __syncthreads();
     if (push) {
         const int4 *items = a.items[l & 1];
-        auto flush = [&]() {
-            bfs_flush(L, next, nitems, (int32_t)L.nq, [&](int32_t i, int32_t &v, int32_t &p, int32_t &len) {
+        auto flush = [&](uint32_t n) {
+            bfs_flush(L, next, nitems, (int32_t)n, [&](int32_t i, int32_t &v, int32_t &p, int32_t &len) {
                 v = L.q.v[i];
                 p = L.q.p[i];
                 len = L.q.len[i];
             });
         };
+        BfsQueueOps ops{L};
+        uint32_t room = BL_PUSH_QUEUE, queued = 0;
         for (int64_t u0 = (int64_t)blockIdx.x * BL_WAVES; u0 * WAVE < T; u0 += (int64_t)gridDim.x * BL_WAVES) {
+            if (queue_is_full<BL_PUSH_QUEUE, BL_TPB>(room, queued, ops)) {
+                flush(queued);
+                if (t == 0) L.nq = 0;
+                __syncthreads();
+            }
             const int64_t tb = (u0 + wv) * WAVE;
             if (tb < T) {
                 const int32_t t0 = (int32_t)tb, tt = t0 + lane;
@@ -238,18 +253,13 @@ __global__ __launch_bounds__(BL_TPB, 8) void k_bfs_level(BfsArgs a, int32_t l)
                     }
                 }
             }
-            __syncthreads();
-            if (L.nq > BL_PUSH_QUEUE - BL_TPB) {
-                flush();
-                if (t == 0) L.nq = 0;
-                __syncthreads();
-            }
         }
         if (gt < a.nwords) {
             if (f0) a.vis[gt] |= f0;
             clr[gt] = 0u;
         }
-        if (L.nq) flush();
+        __syncthreads();  // (nothing is queued after it)
+        if (L.nq) flush(L.nq);
     } else if (bfs_stream(a, c)) {  // (k_bfs_stream has found the level)
         if (gt < a.nwords) {
             if (f0) a.vis[gt] |= f0;

@@ -3,8 +3,9 @@ oracle: exact levels, parents and frontier sizes.
 
 The graphs sit at the edges of its units: rows per wave (64, 256), entries a
 lane looks at alone (1 + 8), the wave's rounds (64, then 512 and 4096 entries
-of a row), found vertices queued per workgroup (1024 in pull, 4096 in push),
-levels launched ahead of the host (8), vertices that no edge leaves."""
+of a row), levels launched ahead of the host (8), vertices that no edge leaves;
+two hubs of more than 2^20 vertices put more found vertices into a workgroup
+than its queue holds (1024 in pull, 4096 in push: emptied between turns)."""
 import numpy as np
 import pytest
 
@@ -47,7 +48,7 @@ def graphs():
     yield "path 700", graph(700, np.arange(699), np.arange(1, 700))
     for n in (63, 64, 65, 255, 256, 257, 1025):
         yield f"random {n}", graph(n, rng.integers(0, n, 2 * n), rng.integers(0, n, 2 * n))
-    # every vertex reached from one hub: more than the queues hold; and back
+    # every vertex reached from one hub in one turn, and back
     n = 9000
     yield "star 9000", graph(n, np.full(n - 1, 4500), np.setdiff1d(np.arange(n), [4500]))
     # rows of 9, 10, 73, 74, 600 and 5000 entries whose only early column in
@@ -87,3 +88,22 @@ def test_bfs_wide_rows_per_turn(torch):
     for policy, th3 in (("auto", 0.0), ("pull", 0.0), ("auto", 0.05)):
         check(ctx, A, oa, n - 1, policy, th3, f"wide {policy} th3={th3}")
         check(ctx, B, ob, 7, policy, th3, f"small after wide {policy} th3={th3}")
+
+
+def test_bfs_queues_overflow(torch):
+    """A frontier of two hubs that finds 1.4M vertices: in push every workgroup
+    takes about eight turns of 1024 entries and queues some 5,500 of the
+    vertices, in pull more of them than its queue holds, so that the next
+    level has no list (auto with th3: it is written from the bitmap)."""
+    n = (1 << 20) + 500_003
+    rng = wl.rng_for(wl.W_RAND, 112, 0)
+    hub, other = n // 3, n // 2
+    leaves = np.setdiff1d(np.arange(1, n), [hub, other])
+    one, two = rng.random(leaves.size) < 0.7, rng.random(leaves.size) < 0.7
+    a = graph(n, np.concatenate([[0, 0], np.full(one.sum(), hub), np.full(two.sum(), other)]),
+              np.concatenate([[hub, other], leaves[one], leaves[two]]))
+    A, om = gpu_matrix(a), oracle_matrix(a)
+    ctx = dbs.Context(A)
+    for s in (0, int(leaves[one & two][-1])):
+        for policy, th3 in (("push", 0.0), ("pull", 0.0), ("auto", 0.0), ("auto", 0.01), ("auto", 2.0)):
+            check(ctx, A, om, s, policy, th3, f"hubs source={s} {policy} th3={th3}")
