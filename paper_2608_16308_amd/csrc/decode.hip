@@ -112,22 +112,22 @@ __device__ __forceinline__ void spread4(uint32_t (&v)[4], uint32_t nib)
     v[3] = b3 ? a3 : 0u;
 }
 
-// The lane's four x (bytes `off` from the vector block's first) of its token;
-// RAG: zeros past the `left` columns the block has.
+// The lane's four x of its token, at xb; RAG: zeros past the `left` columns
+// the vector block has.
 template <int VB, bool RAG>
-__device__ __forceinline__ Vals4<VB> load_x4(const uint8_t *xb, uint32_t off, int32_t left)
+__device__ __forceinline__ Vals4<VB> load_x4(const uint8_t *xb, int32_t left)
 {
     if (RAG && left < BS) {
         const int32_t c0 = (lane_id() & 3) * 4;
         uint32_t w[VB];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) put4<VB>(w, i, c0 + i < left ? val_at<VB>(xb + off, i) : 0u);
+        for (int i = 0; i < 4; ++i) put4<VB>(w, i, c0 + i < left ? val_at<VB>(xb, i) : 0u);
         Vals4<VB> v;
 #pragma unroll
         for (int i = 0; i < VB; ++i) v.w[i] = w[i];
         return v;
     }
-    return *(const Vals4<VB> *)(xb + off);
+    return *(const Vals4<VB> *)xb;
 }
 
 // Lane r + 16 q takes what lane 4 r + q holds (memory order to operand order).
@@ -169,14 +169,15 @@ __device__ __forceinline__ bool entry_of(const uint8_t *rec, uint64_t d, uint32_
 template <int VB, bool RAG>
 struct MfmaWalk {
     const BatchArgs &a;
+    const uint8_t *xl;      // the lane's x in vector block 0
     uint8_t *tile;          // this wave's LDS: 256 values
     const uint2 *sel;
     double acc[4];
-    uint32_t r, q, lane, xoff, src4;
+    uint32_t r, q, lane, src4;
 
     __device__ __forceinline__ Vals4<VB> x_of(int32_t J) const
     {
-        return load_x4<VB, RAG>((const uint8_t *)a.x + (int64_t)J * BS * VB, xoff, a.n - J * BS);
+        return load_x4<VB, RAG>(xl + (int64_t)J * BS * VB, a.n - J * BS);
     }
     __device__ __forceinline__ static bool any_x(const Vals4<VB> &x)
     {
@@ -341,8 +342,9 @@ __global__ __launch_bounds__(NW *WAVE, VB == 2 ? 6 : 4) void k_rows_mfma(BatchAr
     // row i (a lane without a token loads the first one's x: its sums are not
     // used); operand order: lane r + 16 q holds part q of row or token r
     const uint32_t li = lane >> 2, lp = lane & 3;
-    const uint32_t xoff = ((int32_t)li < a.nb ? li * (uint32_t)a.n * VB : 0u) + lp * 4 * VB;
-    MfmaWalk<VB, RAG> w{a, tiles[wv], sel, {0.0, 0.0, 0.0, 0.0}, r, q, (uint32_t)lane, xoff, (r * 4 + q) * 4};
+    // (64 bits: eight tokens of 2^28 columns are 8 GB in fp32)
+    const uint8_t *xl = (const uint8_t *)a.x + ((int32_t)li < a.nb ? (int64_t)li * a.n * VB : 0) + lp * 4 * VB;
+    MfmaWalk<VB, RAG> w{a, xl, tiles[wv], sel, {0.0, 0.0, 0.0, 0.0}, r, q, (uint32_t)lane, (r * 4 + q) * 4};
     // the wave's share of each class of the block row's blocks
     int32_t cb[MC_COUNT][2];
 #pragma unroll

@@ -149,3 +149,30 @@ def test_fp16_subnormals(torch):
     X = np.where(rng.random((3, n)) < 0.5, rng.uniform(1, 100, (3, n)), 0).astype(np.float16)
     X[1] = (rng.integers(0, 1024, n) * 2.0 ** -24).astype(np.float16)         # and a subnormal activation
     check(dbs.Context(A), A, om, X, "fp16 subnormals")
+
+
+@pytest.mark.slow
+@pytest.mark.parametrize("dtype,n", [(np.float32, 160_000_003), (np.float16, 310_000_000)])
+def test_x_of_more_than_4_gib(torch, dtype, n):
+    """Eight activations whose last one begins beyond 2^32 bytes of x."""
+    rng = wl.rng_for(wl.W_RAND, 125, n)
+    m, J = 20, np.array([0, 1, 777, n // 32, (n - 1) // 16 - 1, (n - 1) // 16], np.int64)
+    assert 7 * n * np.dtype(dtype).itemsize > 1 << 32
+    cols = (J[:, None] * 16 + np.arange(16)).reshape(-1)
+    cols = cols[cols < n]
+    W = np.where(rng.random((m, cols.size)) < 0.5, rng.uniform(0.1, 1, (m, cols.size)), 0).astype(dtype)
+    X = rng.uniform(0.1, 1, (8, cols.size)).astype(dtype)
+    X[:, ::3] = 0
+    r, c = np.nonzero(W)
+    A = gpu_matrix(wl.csr_from_coo(m, n, r, cols[c], W[r, c]))
+    ctx = dbs.Context(A)
+    x = torch.zeros((8, n), dtype=torch.float32 if dtype == np.float32 else torch.float16, device="cuda:0")
+    x[:, torch.from_numpy(cols).cuda()] = to_dev(X)
+    log(f"x of {x.numel() * x.element_size() >> 20} MiB, {dtype.__name__}")
+    Y32 = torch.empty((8, m), dtype=torch.float32, device="cuda:0")
+    ctx.spmm_dense(A, x, Y32=Y32)
+    torch.cuda.synchronize()
+    W64, X64 = W.astype(np.float64), X.astype(np.float64)
+    ref, S = X64 @ W64.T, np.abs(X64) @ np.abs(W64).T
+    for b in range(8):
+        assert oracle.within_tol(Y32[b].cpu().numpy(), ref[b], S[b], REL_TOL).all(), f"vector {b}"
