@@ -30,8 +30,9 @@ namespace dbs {
 // in LDS, an entry per lane.
 //
 // Zeros stand for absent entries and inactive x, which only holds for finite
-// numbers: a wave whose sums are not all finite takes its blocks again, entry
-// by entry with both masks (0 * inf must not reach a sum).
+// numbers (0 * inf must not reach a sum): a wave whose sums are not all finite
+// takes its blocks again, those whose own product is not finite with both
+// masks.
 //
 // Bound: by the records streamed once (4096 x 14336 fp16 half pruned, eight
 // tokens: 117 MB in 27 us); four kernels with a lane per row and a loop over
@@ -186,7 +187,9 @@ struct MfmaWalk {
         for (int k = 0; k < VB; ++k) any |= x.w[k];
         return ballot((any & (VB == 4 ? 0x7FFFFFFFu : 0x7FFF7FFFu)) != 0u) != 0;
     }
-    __device__ __forceinline__ void multiply(const uint32_t (&aw)[VB], const Vals4<VB> &x)
+    // False (CHECK only), and nothing added: the block's product is not finite.
+    template <bool CHECK>
+    __device__ __forceinline__ bool multiply(const uint32_t (&aw)[VB], const Vals4<VB> &x)
     {
         uint32_t xw[VB];
 #pragma unroll
@@ -200,17 +203,59 @@ struct MfmaWalk {
             for (int k = 0; k < 4; ++k)
                 p = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(aw[k]), __uint_as_float(xw[k]), p, 0, 0, 0);
         }
+        if constexpr (CHECK) {
+            bool fin = true;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) fin = fin && __builtin_isfinite(p[i]);
+            if (ballot((int32_t)r < a.nb && !fin)) return false;
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[i] += (double)p[i];
+        return true;
+    }
+
+    // One block with both masks: only products of a stored entry and an
+    // active x are formed.  A lane holds the entries of row r in columns 4 q
+    // .. + 3 and sums their products for one token after the other; the four
+    // sums of a row go to the lane whose accumulators hold it.
+    __device__ __forceinline__ void masked_block(int32_t J, uint64_t d)
+    {
+        const uint8_t *rec = a.pay + desc_off(d);
+        uint32_t av[4], have = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            av[c] = 0u;
+            if (entry_of<VB>(rec, d, r, q * 4 + (uint32_t)c, av[c])) have |= 1u << c;
+        }
+        for (int32_t tk = 0; tk < a.nb; ++tk) {
+            const uint8_t *xp = (const uint8_t *)a.x + (int64_t)tk * a.n * VB;
+            float s = 0.f;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int32_t j = J * BS + (int32_t)q * 4 + c;
+                const uint32_t xr = j < a.n ? val_at<VB>(xp, j) : 0u;
+                if (((have >> c) & 1u) && (xr & (VB == 4 ? 0x7FFFFFFFu : 0x7FFFu)))
+                    s = fmaf(val_f<VB>(av[c]), val_f<VB>(xr), s);
+            }
+            s += __shfl_xor(s, 16, WAVE);
+            s += __shfl_xor(s, 32, WAVE);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float v = __shfl(s, (int)q * 4 + i, WAVE);
+                if ((int32_t)r == tk) acc[i] += (double)v;
+            }
+        }
     }
 
     // Blocks b0 .. b1 - 1 of the list, CLASS their class; everything a group
     // of BD_U blocks needs is loaded while the group before it is multiplied:
     // x and the value array, both in memory order (whole lines), a row
-    // format's row mask and start, a COO block's coordinates.
-    template <int CLASS>
+    // format's row mask and start, a COO block's coordinates.  CHECK: blocks
+    // whose product is not finite are taken with both masks.
+    template <int CLASS, bool CHECK>
     __device__ __forceinline__ void walk(int32_t b0, int32_t b1)
     {
+        constexpr int U = CHECK ? 2 : BD_U;  // (more would cost the first walk its registers)
         for (int32_t base = b0; base < b1; base += WAVE) {
             const int32_t nbk = min(WAVE, b1 - base);
             const int32_t Jl = (int32_t)lane < nbk ? a.col[base + lane] : 0;
@@ -219,12 +264,12 @@ struct MfmaWalk {
             // byte offsets: record; values behind it
             const uint64_t ol = desc_off(dl);
             const uint32_t vl = CLASS == MC_ROWS ? values_at(desc_type(dl), nl) : 0u;
-            uint32_t mn[BD_U], en[BD_U], vn[BD_U][VB], nn[BD_U];
-            uint64_t dn[BD_U];
-            Vals4<VB> xn[BD_U];
+            uint32_t mn[U], en[U], vn[U][VB], nn[U];
+            uint64_t dn[U];
+            Vals4<VB> xn[U];
             auto fetch = [&](int32_t i0) {
 #pragma unroll
-                for (int u = 0; u < BD_U; ++u) {
+                for (int u = 0; u < U; ++u) {
                     const int i = min(i0 + u, nbk - 1);
                     xn[u] = x_of((int32_t)readlane_u32((uint32_t)Jl, i));
                     const uint8_t *rec = a.pay + readlane_u64(ol, i);
@@ -260,12 +305,13 @@ struct MfmaWalk {
                 }
             };
             fetch(0);
-            for (int32_t i0 = 0; i0 < nbk; i0 += BD_U) {
-                uint32_t aw[BD_U][VB];
-                Vals4<VB> x[BD_U];
-                bool act[BD_U];
+            uint64_t masked = 0;
+            for (int32_t i0 = 0; i0 < nbk; i0 += U) {
+                uint32_t aw[U][VB];
+                Vals4<VB> x[U];
+                bool act[U];
 #pragma unroll
-                for (int u = 0; u < BD_U; ++u) {
+                for (int u = 0; u < U; ++u) {
                     x[u] = xn[u];
                     act[u] = i0 + u < nbk && any_x(x[u]);
                     if (!act[u]) continue;
@@ -317,12 +363,26 @@ struct MfmaWalk {
                         }
                     }
                 }
-                if (i0 + BD_U < nbk) fetch(i0 + BD_U);
+                if (i0 + U < nbk) fetch(i0 + U);
 #pragma unroll
-                for (int u = 0; u < BD_U; ++u)
-                    if (act[u]) multiply(aw[u], x[u]);
+                for (int u = 0; u < U; ++u)
+                    if (act[u] && !multiply<CHECK>(aw[u], x[u])) masked |= 1ull << (i0 + u);
+            }
+            if constexpr (CHECK) {
+                for (; masked; masked &= masked - 1ull) {
+                    const int i = ctz64(masked);
+                    masked_block((int32_t)readlane_u32((uint32_t)Jl, i), readlane_u64(dl, i));
+                }
             }
         }
+    }
+
+    template <bool CHECK> __device__ __forceinline__ void walk_all(const int32_t (&cb)[MC_COUNT][2])
+    {
+        walk<MC_DENSE, CHECK>(cb[MC_DENSE][0], cb[MC_DENSE][1]);
+        walk<MC_ROWS, CHECK>(cb[MC_ROWS][0], cb[MC_ROWS][1]);
+        walk<MC_COO, CHECK>(cb[MC_COO][0], cb[MC_COO][1]);
+        walk<MC_OTHER, CHECK>(cb[MC_OTHER][0], cb[MC_OTHER][1]);
     }
 };
 
@@ -354,10 +414,7 @@ __global__ __launch_bounds__(NW *WAVE, VB == 2 ? 6 : 4) void k_rows_mfma(BatchAr
         cb[k][0] = h0 + (int32_t)((int64_t)at * cnt / of);
         cb[k][1] = h0 + (int32_t)((int64_t)(at + 1) * cnt / of);
     }
-    w.template walk<MC_DENSE>(cb[MC_DENSE][0], cb[MC_DENSE][1]);
-    w.template walk<MC_ROWS>(cb[MC_ROWS][0], cb[MC_ROWS][1]);
-    w.template walk<MC_COO>(cb[MC_COO][0], cb[MC_COO][1]);
-    w.template walk<MC_OTHER>(cb[MC_OTHER][0], cb[MC_OTHER][1]);
+    w.template walk_all<false>(cb);
     double (&acc)[4] = w.acc;
     // lane: rows 4 q + i, token r
     bool fin = true;
@@ -366,23 +423,7 @@ __global__ __launch_bounds__(NW *WAVE, VB == 2 ? 6 : 4) void k_rows_mfma(BatchAr
     if (ballot(tok && !fin)) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[i] = 0.0;
-        for (int k = 0; k < MC_COUNT; ++k)
-        for (int32_t b = cb[k][0]; b < cb[k][1]; ++b) {
-            const uint64_t d = a.desc[b];
-            const int32_t J = a.col[b];
-            const uint8_t *rec = a.pay + desc_off(d);
-            for (int i = 0; i < 4; ++i) {
-                float s = 0.f;
-                for (int c = 0; c < 16; ++c) {
-                    const int32_t j = J * BS + c;
-                    const uint32_t xr = tok && j < a.n ? val_at<VB>((const uint8_t *)a.x + (int64_t)r * a.n * VB, j) : 0u;
-                    uint32_t raw = 0u;
-                    if ((xr & (VB == 4 ? 0x7FFFFFFFu : 0x7FFFu)) && entry_of<VB>(rec, d, q * 4 + (uint32_t)i, (uint32_t)c, raw))
-                        s = fmaf(val_f<VB>(raw), val_f<VB>(xr), s);
-                }
-                acc[i] += (double)s;
-            }
-        }
+        w.template walk_all<true>(cb);
     }
     if (r < 8) {
 #pragma unroll

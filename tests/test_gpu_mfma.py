@@ -139,6 +139,61 @@ def test_not_finite(torch, dtype):
             assert np.allclose(g[ok], y64[ok], rtol=0, atol=1e-5 * n)
 
 
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("force", [-1, 0, 1, 2, 3, 4])
+def test_not_finite_in_long_block_rows(torch, dtype, force):
+    """The second walk of a wave whose sums are not finite: every block class,
+    more than 64 blocks per wave, a ragged last block, one block with an
+    infinity and all of them."""
+    rng = wl.rng_for(wl.W_RAND, 126, force + 1)
+    m, n = 40, 5000
+    p = np.kron(rng.choice([0.02, 0.1, 0.3, 0.6, 1.0], (3, 313)), np.ones((16, 16)))[:m, :n]
+    r, c = np.nonzero(rng.random((m, n)) < p)
+    a = wl.csr_from_coo(m, n, r, c, wl._nonzero_uniform(rng, -1.0, 1.0, r.size, dtype=dtype))
+    opts = dbs.default_opts(force_type=force, th1=250 if force == 4 else 128)
+    for case in ("x", "A", "last", "all of x"):
+        X = activations(3, n, dtype, 30, 0.5)
+        if case == "x":
+            X[2, 4001] = np.inf
+        elif case == "A":
+            a.vals[[7, r.size // 2]] = [np.nan, -np.inf]
+        elif case == "last":
+            X[0, n - 1] = -np.inf
+        else:
+            X[:] = np.where(X > 0.5, np.inf, X)
+        A, om = gpu_matrix(a, opts), oracle_matrix(a)
+        Y32 = torch.empty((3, m), dtype=torch.float32, device="cuda:0")
+        dbs.Context(A).spmm_dense(A, to_dev(X), Y32=Y32)
+        torch.cuda.synchronize()
+        for b in range(3):
+            y64, S = oracle_sums(om, X[b])
+            g = Y32[b].cpu().numpy()
+            log(f"{case}, force={force} {dtype.__name__}, vector {b}: {np.sum(~np.isfinite(y64))} rows not finite")
+            assert np.array_equal(np.isnan(g), np.isnan(y64))
+            assert np.array_equal(g[np.isinf(y64)], y64[np.isinf(y64)]) and not np.isinf(g[np.isfinite(y64)]).any()
+            ok = np.isfinite(y64)
+            assert oracle.within_tol(g[ok], y64[ok], S[ok], REL_TOL).all()
+
+
+def test_fp32_subnormals(torch):
+    """Products and block sums below the smallest normal number are kept."""
+    rng = wl.rng_for(wl.W_RAND, 127, 0)
+    m, n = 64, 128
+    r, c = np.nonzero(rng.random((m, n)) < 0.5)
+    v = (rng.uniform(0.5, 1, r.size) * 1e-20).astype(np.float32)
+    a = wl.csr_from_coo(m, n, r, c, v)
+    X = np.where(rng.random((3, n)) < 0.5, rng.uniform(0.5, 1, (3, n)) * 1e-20, 0).astype(np.float32)
+    A, om = gpu_matrix(a), oracle_matrix(a)
+    Y = dbs.Context(A).spmm_dense(A, to_dev(X))
+    torch.cuda.synchronize()
+    for b in range(3):
+        y64, _ = oracle_sums(om, X[b])
+        # each of at most 128 products, and each block's sum, rounds by half of 2^-149
+        d = np.abs(Y[b].cpu().numpy().astype(np.float64) - y64).max()
+        log(f"fp32 subnormals, vector {b}: largest difference {d / 2.0 ** -149:.1f} of 2^-149, largest sum {y64.max():.2e}")
+        assert d <= 140 * 2.0 ** -149
+
+
 def test_fp16_subnormals(torch):
     rng = wl.rng_for(wl.W_RAND, 124, 0)
     m, n = 64, 128
