@@ -472,12 +472,18 @@ bool rows_mfma_fits(const DevMatrix &A) { return A.ab_col != nullptr; }
 // holds at once.  fp16, eight tokens, us with 16 waves / with eight and as many
 // as the device holds: 4096 x 14336 31 / 35, 700 x 7000 13 / 18, 3000 x 3000
 // 15 / 22, 11008 x 4096 35 / 25, 5003 x 7001 37 / 26.
+// Short block rows take four waves; where there are 2048 and more of at most 16
+// blocks, one: a workgroup's launch and exchange then cost more than its
+// blocks (four tokens, four waves / one: 10^6 x 16 fp16 137 / 48, fp32 207 /
+// 65; 64000 x 256 fp32 24 / 19; at 2048 rows of 16 they are equal, with 1024
+// rows or 32 blocks four are faster).
 struct MfmaShape {
     int waves;
     int32_t parts;
 };
 static MfmaShape mfma_shape(const DevMatrix &A)
 {
+    if (A.nbr >= 2048 && A.nblk <= (int64_t)A.nbr * 16) return {1, 1};
     if (A.nbr <= 0 || A.nblk < (int64_t)A.nbr * 128) return {4, 1};
     const int waves = A.nbr <= 256 ? 16 : 8;
     // 8-wave workgroups per compute unit: 3 at no more than 80 registers
@@ -518,11 +524,13 @@ hipError_t launch_rows_mfma(const DevMatrix &A, const DevCtx &C, double *yacc, i
     if (A.dtype == 1) {
         if (nw == 16) DBS_MFMA_RAG(2, 16);
         else if (nw == 8) DBS_MFMA_RAG(2, 8);
-        else DBS_MFMA_RAG(2, 4);
+        else if (nw == 4) DBS_MFMA_RAG(2, 4);
+        else DBS_MFMA_RAG(2, 1);
     } else {
         if (nw == 16) DBS_MFMA_RAG(4, 16);
         else if (nw == 8) DBS_MFMA_RAG(4, 8);
-        else DBS_MFMA_RAG(4, 4);
+        else if (nw == 4) DBS_MFMA_RAG(4, 4);
+        else DBS_MFMA_RAG(4, 1);
     }
 #undef DBS_MFMA_RAG
 #undef DBS_MFMA

@@ -94,10 +94,11 @@ def test_block_classes(torch, dtype, force):
 
 @pytest.mark.parametrize("dtype", [np.float16, np.float32])
 @pytest.mark.parametrize("m,n,keep", [(16, 2048, 0.5), (33, 4100, 0.4), (700, 3000, 0.1), (4096, 2100, 0.06),
-                                      (17, 16, 0.5), (3290, 2064, 0.3)])
+                                      (17, 16, 0.5), (3290, 2064, 0.3), (32760, 250, 0.2), (32744, 250, 0.2),
+                                      (32760, 16, 0.2), (40000, 33, 0.5)])
 def test_shapes(torch, dtype, m, n, keep):
     """One block row in many parts, a few, the 16-wave shape (256 block rows),
-    short rows, ragged both ways."""
+    short rows, ragged both ways, many short rows (a wave each from 2048 on)."""
     rng = wl.rng_for(wl.W_RAND, 122, m, n)
     mask = rng.random((m, n)) < keep
     mask[16:32] &= n > 100                     # a block row without blocks in the narrow case
