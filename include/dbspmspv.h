@@ -373,10 +373,16 @@ dbs_status dbs_spmspv_noalloc(const dbs_matrix *A, dbs_semiring sr, int32_t x_nn
  * (Sec. 4.1).  d_y_dense receives all m outputs in A's dtype (rows with no
  * active product are 0), rounded to nearest even from the fp64 sum.
  * d_y_f32 (NULL allowed) receives the same sums rounded to fp32.
- * With AUTO and th3 <= 0, or with pull, no selector runs: the entries are
- * streamed (most of them in COO blocks) or all blocks multiplied (eight
- * entries per block and more); stats then reports what the selector would
- * have counted and chosen.  th3 > 0 applies the paper's rule on the device.
+ * With AUTO and th3 <= 0, or with pull, no selector runs where one pass over
+ * the matrix is the faster way whatever x: a matrix without COO blocks (n a
+ * multiple of 16, x 16-byte aligned) multiplies the blocks of active vector
+ * blocks, one with most entries in COO blocks streams its entries, another
+ * with eight entries per block and more multiplies all blocks (up to 32 MiB
+ * of them, 48 for n a multiple of 16; fp16 blocks of at most 64 entries on
+ * average whatever their number; not with one or two blocks per block row).
+ * stats then reports what the selector would have counted and chosen.  All
+ * other calls, and th3 > 0, let the device choose as in dbs_spmspv (but a
+ * matrix without COO blocks takes pull, see DBS_TH3_DEFAULT).
  * F32 and F16 matrices only.                                               */
 dbs_status dbs_spmspv_dense(dbs_ctx *ctx, const dbs_matrix *A, const void *d_x_dense,
                             dbs_path path, float th3, void *d_y_dense, float *d_y_f32,
@@ -391,11 +397,14 @@ dbs_status dbs_spmspv_dense(dbs_ctx *ctx, const dbs_matrix *A, const void *d_x_d
  *   nb         1 .. DBS_MAX_BATCH
  * For a matrix of eight entries per block and more the nb vectors share one
  * pass over the blocks on the matrix cores (path reports pull; N_nzblk in
- * stats counts the union of the vectors' vector blocks).  Two fp32 vectors on
- * a matrix of 256 block rows and more without COO blocks share a pass with a
- * lane per row.  Otherwise, or for nb = 1, the vectors are taken one
- * dbs_spmspv_dense call each.  A call that needs them (statistics, the
- * lane-per-row pass, block rows taken in parts)
+ * stats counts the union of the vectors' vector blocks).  On a matrix without
+ * COO blocks some calls share a pass with a lane per row instead: those with
+ * fewer than eight entries per block, and with 256 block rows and more two
+ * fp32 vectors or, where block rows hold less than two blocks, up to four fp32
+ * or two fp16 vectors.  Otherwise (COO blocks and fewer than eight entries per
+ * block), or for nb = 1, the vectors are taken one dbs_spmspv_dense call each.
+ * A call that needs them (statistics, the lane-per-row pass, block rows taken
+ * in parts)
  * allocates, once, DBS_MAX_BATCH padded x copies and fp64 accumulator sets
  * for the context's largest shape (kept until dbs_ctx_destroy).             */
 #define DBS_MAX_BATCH 8

@@ -790,6 +790,29 @@ extern "C" dbs_status dbs_spmspv(dbs_ctx *ctx, const dbs_matrix *A, dbs_semiring
     return DBS_OK;
 }
 
+// One activation on a matrix that the matrix-core pass can take: whether that
+// is the faster way.  It multiplies every block, at the copy rate; the scan
+// and the traversal cost 15-20 us more to launch but only visit active vector
+// blocks, an uneven share of the bytes.  With sizes for which no other pass
+// applies, 3-40% active at random, us before / matrix cores:
+//   2001 x 3001   half pruned  fp16 (7 MiB) 25-34 / 12-13, fp32 (13 MiB) 27-34 / 12-14
+//   5003 x 7001   70% pruned   fp16 (27 MiB) 28-46 / 25-28, fp32 (46 MiB) 29-50 / 36-53
+//   7999 x 7999   70% pruned   fp16 (48 MiB) 24-44 / 40-44, fp32 (85 MiB) 26-47 / 42-60
+//   8000 x 8000   80% pruned   fp16 (36 MiB) 34-54 / 26-32, fp32 (60 MiB) 36-57 / 36-59
+//   4500 x 4000   half pruned  fp32 (38 MiB) 28-42 / 20-31
+//   16384 x 16384 80% pruned   fp16 (150 MiB) 75-150 / 90-95, fp32 (252 MiB) 84-187 / 146-210
+// -- up to 32 MiB, 48 with whole vector blocks (x is then loaded aligned and
+// without a test), and in fp16 where a block's values fit half a run.  Block
+// rows of one or two blocks keep too few of a wave's loads in flight (10^6 x
+// 16 fp16 41 / 48, fp32 41 / 64; 500000 x 32 fp16 32 / 28, fp32 33 / 38).
+static bool mfma_for_one(const dbs_matrix *A)
+{
+    if (!rows_mfma_fits(A->d)) return false;
+    const int64_t nblk = A->d.nblk, nnz = A->info.nnz, vb = dtype_bytes((dbs_dtype)A->d.dtype);
+    if (nblk < (int64_t)A->d.nbr * (vb == 2 ? 2 : 3)) return false;
+    return nblk * 48 + nnz * vb <= ((A->d.n % BS ? 32 : 48) << 20) || (vb == 2 && nnz <= nblk * (MC_RUN / 2));
+}
+
 extern "C" dbs_status dbs_spmspv_dense(dbs_ctx *ctx, const dbs_matrix *A, const void *d_x_dense,
                                        dbs_path path, float th3, void *d_y_dense, float *d_y_f32,
                                        dbs_call_stats *stats)
@@ -818,7 +841,7 @@ extern "C" dbs_status dbs_spmspv_dense(dbs_ctx *ctx, const dbs_matrix *A, const 
         if (stats)
             LAUNCH(ctx, DBS_K_SCAN, launch_scan(A->d, ctx->c, p, (double)norm_th3(th3), spread_th3(th3), s));
         LAUNCH(ctx, DBS_K_FINALIZE, launch_finalize_dense(A->d, ctx->c, mode, d_y_dense, d_y_f32, s));
-    } else if (rows_mfma_fits(A->d) && path != DBS_PATH_PUSH && !(path == DBS_PATH_AUTO && th3 > 0.f)) {
+    } else if (mfma_for_one(A) && path != DBS_PATH_PUSH && !(path == DBS_PATH_AUTO && th3 > 0.f)) {
         // blocks of many entries: all of them on the matrix cores, whatever
         // the selector would choose (a call that asks for statistics lets the
         // scan count and choose afterwards, and clears what that wrote)
@@ -863,10 +886,14 @@ extern "C" dbs_status dbs_spmm_dense(dbs_ctx *ctx, const dbs_matrix *A, int32_t 
     if (!d_x || !d_y) return dbs_fail(DBS_ERR_ARG, "NULL activations or outputs");
     const int mode = A->d.dtype == DBS_F16 ? M_F16 : M_F32;
     const size_t vb = A->d.dtype == DBS_F16 ? 2 : 4;
-    // the matrix-core pass, but for two fp32 vectors on blocks that the shared
-    // pass below takes (11008 x 4096: 43 against 49 us)
-    const bool two_vec = nb == 2 && A->d.dtype == DBS_F32 && A->d.nheavy == A->d.nblk && A->d.nbr >= 256;
-    const bool mfma = nb > 1 && rows_mfma_fits(A->d) && !two_vec;
+    // the matrix-core pass, but on a matrix without COO blocks the shared pass
+    // below for two fp32 vectors (11008 x 4096: 43 against 49 us) and, where
+    // block rows hold one block, for two fp16 and up to four fp32 vectors (10^6
+    // x 16: 41 against 48 and 56 against 63)
+    const bool f32 = A->d.dtype == DBS_F32, one = A->d.nblk < (int64_t)A->d.nbr * 2;
+    const int32_t most = f32 ? (one ? 4 : 2) : (one ? 2 : 0);
+    const bool shared = A->d.nheavy == A->d.nblk && A->d.nbr >= 256 && nb <= most;
+    const bool mfma = nb > 1 && rows_mfma_fits(A->d) && !shared;
     if (!mfma && (nb == 1 || A->d.nheavy < A->d.nblk || A->d.nblk == 0)) {
         // one vector, or a matrix of COO blocks with few entries each (their
         // segment loop is single-vector): one dense-activation call per vector

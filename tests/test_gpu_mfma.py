@@ -110,6 +110,49 @@ def test_shapes(torch, dtype, m, n, keep):
         check(ctx, A, om, activations(nb, n, dtype, 10 + nb, 0.2), f"{dtype.__name__} {m}x{n} keep={keep} nb={nb}")
 
 
+def layer(m, n, keep, dtype, key):
+    """m x n, an entry with probability `keep`; block edges may be cut off."""
+    rng = wl.rng_for(wl.W_RAND, 128, key)
+    mask = rng.random((m, n)) < keep
+    if m % 16 and n % 16:
+        mask[m // 16 * 16:, n // 16 * 16:] = False  # (the corner block would be a COO block)
+    r, c = np.nonzero(mask)
+    return wl.csr_from_coo(m, n, r, c, wl._nonzero_uniform(rng, -1.0, 1.0, r.size, dtype=dtype))
+
+
+@pytest.mark.parametrize("dtype,m,n,nbs", [(np.float32, 4100, 150, (2,)), (np.float32, 4100, 16, (2, 3, 4)),
+                                           (np.float16, 4100, 16, (2,))])
+def test_shared_lane_per_row_pass(torch, dtype, m, n, nbs):
+    """No COO block, 256 block rows and more: two fp32 vectors, and up to four
+    fp32 or two fp16 ones where block rows hold one block; and on either side
+    of the rule the matrix cores, on the same context."""
+    a = layer(m, n, 0.85, dtype, n)
+    A, om = gpu_matrix(a), oracle_matrix(a)
+    assert A.info()["blocks_by_type"]["coo"] == 0 and A.info()["nbr"] >= 256
+    ctx = dbs.Context(A)
+    for nb in (*nbs, max(nbs) + 1, 8, nbs[0]):
+        check(ctx, A, om, activations(nb, n, dtype, 40 + nb), f"shared {dtype.__name__} {m}x{n} nb={nb}")
+
+
+@pytest.mark.parametrize("dtype,m,n,keep", [(np.float32, 2803, 5008, 0.95), (np.float32, 2003, 4499, 0.9),
+                                            (np.float16, 2603, 6499, 0.95), (np.float32, 3000, 32, 0.3)])
+def test_one_vector_beyond_the_matrix_core_pass(torch, dtype, m, n, keep):
+    """One activation on layers that the matrix-core pass leaves to the scan
+    and the traversal: more than 32 or 48 MiB of blocks, two blocks per block
+    row; several vectors on them."""
+    rng = wl.rng_for(wl.W_RAND, 129, m, n)
+    mask = rng.random((m, n)) < keep
+    mask[:16, :16] = False
+    mask[3, 5] = True                      # (a COO block)
+    r, c = np.nonzero(mask)
+    a = wl.csr_from_coo(m, n, r, c, wl._nonzero_uniform(rng, -1.0, 1.0, r.size, dtype=dtype))
+    A, om = gpu_matrix(a), oracle_matrix(a)
+    ctx = dbs.Context(A)
+    for nb in (1, 3):
+        for density in (0.002, 0.3):
+            check(ctx, A, om, activations(nb, n, dtype, 70 + nb, density), f"large {dtype.__name__} {m}x{n} nb={nb} {density}")
+
+
 @pytest.mark.parametrize("dtype", [np.float16, np.float32])
 def test_not_finite(torch, dtype):
     """Infinities and NaN reach the rows that hold the entry, and no others:
