@@ -294,10 +294,11 @@ def test_spmm_dense_forced_formats_f32(torch, force):
 
 
 def test_spmm_dense_matrix_with_coo_blocks(torch):
-    # a sparse layer has COO blocks: the vectors are taken one call each
+    # COO blocks of about 13 entries each: one matrix-core pass for all vectors
     w = wl.decode_layer(300, 640, keep=0.05)
     A, om = gpu_matrix(w), oracle_matrix(w)
     assert A.info()["blocks_by_type"]["coo"] > 0
+    assert A.info()["nnz"] >= 8 * A.info()["nblk"]
     ctx = dbs.Context(A)
     X = np.stack([wl.decode_activation(640, key=k) for k in range(4)])
     log("spmm decode with COO blocks nb=4")

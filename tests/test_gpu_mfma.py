@@ -32,16 +32,19 @@ def check(ctx, A, om, X, label):
     log(label)
     nb = X.shape[0]
     refs = [oracle_sums(om, X[b]) for b in range(nb)]
-    for rep in range(2):  # (the second finds what the first left in the scratch)
+    # every call finds what the ones before left in the scratch; without
+    # statistics nothing but the pass itself restores it
+    for stats in (False, False, True, False):
         Y32 = torch.full((nb, om.m), -7.0, dtype=torch.float32, device="cuda:0")
         if nb == 1:
-            y, st = ctx.spmspv_dense(A, to_dev(X[0]), y32=Y32[0], stats=True)
-            Y = y[None]
+            out = ctx.spmspv_dense(A, to_dev(X[0]), y32=Y32[0], stats=stats)
         else:
-            Y, st = ctx.spmm_dense(A, to_dev(X), Y32=Y32, stats=True)
+            out = ctx.spmm_dense(A, to_dev(X), Y32=Y32, stats=stats)
         torch.cuda.synchronize()
+        Y, st = out if stats else (out, None)
+        Y = Y[None] if nb == 1 else Y
         blocks = np.unique(np.nonzero((X != 0).any(0))[0] >> 4)
-        assert st["n_nzblk"] == blocks.size, (label, st)
+        assert st is None or st["n_nzblk"] == blocks.size, (label, st)
         for b in range(nb):
             y64, S = refs[b]
             g, g32 = Y[b].cpu().numpy(), Y32[b].cpu().numpy()
@@ -132,6 +135,33 @@ def test_shared_lane_per_row_pass(torch, dtype, m, n, nbs):
     ctx = dbs.Context(A)
     for nb in (*nbs, max(nbs) + 1, 8, nbs[0]):
         check(ctx, A, om, activations(nb, n, dtype, 40 + nb), f"shared {dtype.__name__} {m}x{n} nb={nb}")
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("force", [1, 2, 3, 4])
+def test_forced_formats_of_few_entries(torch, dtype, force):
+    """Fewer than eight entries per block and no COO block: the lane-per-row
+    pass for 2, 4 and 8 vectors."""
+    a = layer(150, 330, 0.02, dtype, 500 + force)
+    A, om = gpu_matrix(a, dbs.default_opts(force_type=force)), oracle_matrix(a)
+    assert A.info()["nnz"] < 8 * A.info()["nblk"] and A.info()["blocks_by_type"]["coo"] == 0
+    ctx = dbs.Context(A)
+    for nb in (1, 2, 3, 4, 5, 8):
+        check(ctx, A, om, activations(nb, 330, dtype, 50 + nb), f"few entries force={force} {dtype.__name__} nb={nb}")
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("th0", [32, 6])
+def test_few_entries_with_coo_blocks(torch, dtype, th0):
+    """Fewer than eight entries per block, COO blocks among them: one call per
+    vector (th0 = 6: less than half of the entries in COO blocks)."""
+    a = layer(150, 330, 0.025, dtype, 510)
+    A, om = gpu_matrix(a, dbs.default_opts(th0=th0)), oracle_matrix(a)
+    i = A.info()
+    assert i["nnz"] < 8 * i["nblk"] and i["blocks_by_type"]["coo"] > 0
+    ctx = dbs.Context(A)
+    for nb in (1, 2, 5):
+        check(ctx, A, om, activations(nb, 330, dtype, 60 + nb), f"few entries th0={th0} {dtype.__name__} nb={nb}")
 
 
 @pytest.mark.parametrize("dtype,m,n,keep", [(np.float32, 2803, 5008, 0.95), (np.float32, 2003, 4499, 0.9),
