@@ -711,7 +711,7 @@ dbs_status spmspv_launches(const dbs_matrix *A, DevCtx &c, hipStream_t s, int mo
     const bool items = entries && launch_path != DBS_PATH_PULL && x_nnz <= A->d.nbc;
     if (items || (entries && launch_path == DBS_PATH_PULL)) {
         st = run(DBS_K_SCATTER, [&] {
-            return items ? launch_entry_scatter(A->d, c, mode, x_nnz, d_x_idx, d_x_val, s)
+            return items ? launch_entry_scatter(A->d, c, mode, x_nnz, d_x_idx, d_x_val, launch_path == DBS_PATH_AUTO, s)
                          : launch_scatter(A->d, c, mode, x_nnz, d_x_idx, d_x_val, s);
         });
         if (st != DBS_OK) return st;

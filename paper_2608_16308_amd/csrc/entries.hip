@@ -51,16 +51,19 @@ __device__ __forceinline__ bool ev_admit(const uint32_t *omask, int32_t compleme
 // items and tasks with one 64-bit atomic, so that
 // items ascend in their first tasks without a scan over the workgroups.  A
 // repeated index keeps the occurrence whose mask atomic found its bit clear.
+// COUNT: the nonzero vector blocks and the distinct indices are added up in
+// C_ECOUNT, from what the mask atomics found, so that the traversal can choose
+// without reading the masks.
 constexpr int ES_TPB = 256;
 
-template <int MODE>
+template <int MODE, bool COUNT>
 __global__ __launch_bounds__(ES_TPB) void k_entry_scatter(const int32_t *__restrict__ xi, const void *__restrict__ xv,
                                                           int32_t k, int32_t n, void *__restrict__ xd,
                                                           uint32_t *__restrict__ xmask,
                                                           const int32_t *__restrict__ ce_ptr, int4 *__restrict__ items,
                                                           int32_t *__restrict__ counters)
 {
-    __shared__ uint64_t s_tot[ES_TPB / WAVE];
+    __shared__ uint64_t s_tot[ES_TPB / WAVE], s_cnt[ES_TPB / WAVE];
     __shared__ uint64_t s_base;
     const int32_t t = blockIdx.x * ES_TPB + threadIdx.x;
     const int lane = lane_id(), wv = wave_id();
@@ -102,8 +105,19 @@ __global__ __launch_bounds__(ES_TPB) void k_entry_scatter(const int32_t *__restr
     const int last = above ? ctz64(above) - 1 : WAVE - 1;
     uint32_t old = 0;
     if (ok && lane == last) old = atomicOr(&xmask[w], incl);
+    if constexpr (COUNT) {
+        // the vector blocks that this run's atomic made nonzero
+        const uint32_t was = ok && lane == last ? old : 0xFFFFFFFFu;
+        const uint64_t lo = ballot(!(was & 0xFFFFu) && (incl & 0xFFFFu));
+        const uint64_t hi = ballot(!(was >> 16) && (incl >> 16));
+        if (lane == 0) s_cnt[wv] = (uint64_t)(__popcll(lo) + __popcll(hi));
+    }
     old = (uint32_t)__shfl((int)old, last, WAVE);
-    const bool own = ok && !((old | excl) & bit) && p1 > p0;
+    const bool first = ok && !((old | excl) & bit), own = first && p1 > p0;
+    if constexpr (COUNT) {
+        const uint64_t distinct = ballot(first);
+        if (lane == 0) s_cnt[wv] |= (uint64_t)__popcll(distinct) << 32;
+    }
     const uint64_t mine = own ? (1ull << EV_TASK_BITS) + (uint64_t)(p1 - p0) : 0ull;
     uint64_t inc = mine;
 #pragma unroll
@@ -118,6 +132,14 @@ __global__ __launch_bounds__(ES_TPB) void k_entry_scatter(const int32_t *__restr
 #pragma unroll
         for (int i = 0; i < ES_TPB / WAVE; ++i) tot += s_tot[i];
         s_base = tot ? (uint64_t)atomicAdd((unsigned long long *)&counters[C_EITEMS], (unsigned long long)tot) : 0ull;
+    }
+    if constexpr (COUNT) {
+        if (threadIdx.x == WAVE) {
+            uint64_t cnt = 0;
+#pragma unroll
+            for (int i = 0; i < ES_TPB / WAVE; ++i) cnt += s_cnt[i];
+            if (cnt) atomicAdd((unsigned long long *)&counters[C_ECOUNT], (unsigned long long)cnt);
+        }
     }
     __syncthreads();
     if (own) {
@@ -273,11 +295,9 @@ __device__ __forceinline__ void seg_step(double &sum, uint32_t &ok, uint32_t key
 }
 
 // Copies the masks into the LDS bitmap, 16 bytes per load and BM_U loads in
-// flight per thread, and (COUNT) adds up this thread's nonzero vector blocks
-// and stored indices.
+// flight per thread.
 constexpr int BM_U = 8;
-template <bool COUNT>
-__device__ __forceinline__ void ep_bitmap(const EntryPullArgs &a, uint32_t &nz, uint32_t &pop)
+__device__ __forceinline__ void ep_bitmap(const EntryPullArgs &a)
 {
     const int t = threadIdx.x;
     const int32_t nq = (a.nxw + 3) >> 2;  // groups of four mask words
@@ -299,14 +319,7 @@ __device__ __forceinline__ void ep_bitmap(const EntryPullArgs &a, uint32_t &nz, 
         for (int u = 0; u < BM_U; ++u) {
             const int32_t q = q0 + u * EP_TPB + t;
             if (q >= nq) continue;
-            uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-            if constexpr (COUNT) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    pop += __popc(w[i]);
-                    nz += ((w[i] & 0xFFFFu) ? 1u : 0u) + ((w[i] >> 16) ? 1u : 0u);
-                }
-            }
+            const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
             if (a.fold == 0) {
                 ((uint4 *)ep_bits)[q] = v[u];
             } else if (a.fold == 1) {
@@ -324,17 +337,17 @@ __device__ __forceinline__ void ep_bitmap(const EntryPullArgs &a, uint32_t &nz, 
     }
 }
 
-// DECIDE: push or pull was not settled on the host.  Every workgroup counts
-// N_nzblk and the distinct indices while it copies the masks and applies the
-// selector's rule (Sec. 3.3.1 and the spread rule, as k_scan), so that no
-// scan and no second traversal kernel is launched.
+// DECIDE: push or pull was not settled on the host.  Every workgroup applies
+// the selector's rule (Sec. 3.3.1 and the spread rule, as k_scan) to the
+// blocker's counts before it copies the masks, so that no scan and no second
+// traversal kernel is launched.  (Counting while the masks are copied made
+// every push wait for the copy: 30 of 64 us with 4M columns.)
 template <int MODE, bool DECIDE>
 __global__ __launch_bounds__(EP_TPB) void k_entry_pull(EntryPullArgs a)
 {
     constexpr bool VAL = ev_valued<MODE>();
     __shared__ uint32_t q_col[EP_WAVES][EP_QUEUE], q_ent[EP_WAVES][VAL ? EP_QUEUE : 1];
     __shared__ uint32_t q_ord[EP_WAVES][EP_QUEUE];
-    __shared__ uint32_t s_cnt[EP_WAVES * 2];
     const int t = threadIdx.x, lane = lane_id(), wv = wave_id();
     // the wave's chunks; its first words go out before the bitmap is formed
     const int64_t W = (int64_t)gridDim.x * EP_WAVES, wid = (int64_t)wv * gridDim.x + blockIdx.x;
@@ -345,34 +358,21 @@ __global__ __launch_bounds__(EP_TPB) void k_entry_pull(EntryPullArgs a)
         w[j] = c0 < c1 ? __builtin_nontemporal_load(&a.col[(int64_t)c0 * RE_CHUNK + j * WAVE + lane]) : 0u;
     int32_t ord = c0 < c1 ? a.chord[c0] : 0;
     if (a.scanned && a.counters[C_PATH] != PATH_PULL) return;
-    if (a.fold > 1) {
-        for (int32_t i = t; i < a.nbw; i += EP_TPB) ep_bits[i] = 0u;
-        __syncthreads();
-    }
-    uint32_t nz = 0, pop = 0;
-    ep_bitmap<DECIDE>(a, nz, pop);
     if constexpr (DECIDE) {
-        nz = wave_sum(nz);
-        pop = wave_sum(pop);
-        if (lane == 0) {
-            s_cnt[wv] = nz;
-            s_cnt[EP_WAVES + wv] = pop;
-        }
-    }
-    __syncthreads();
-    if constexpr (DECIDE) {
-        uint32_t N = 0, P = 0;
-#pragma unroll
-        for (int i = 0; i < EP_WAVES; ++i) {
-            N += s_cnt[i];
-            P += s_cnt[EP_WAVES + i];
-        }
+        const uint64_t cnt = *(const uint64_t *)&a.counters[C_ECOUNT];
+        const uint32_t N = (uint32_t)cnt, P = (uint32_t)(cnt >> 32);
         const bool spread = a.th3s > 0.0 && (int64_t)P < 2 * (int64_t)N && (double)N < a.th3s * (double)a.nbc;
         if ((double)N < a.th3 * (double)a.nbc || spread) {
             entry_push<MODE>(a.push, wid, W);
             return;
         }
     }
+    if (a.fold > 1) {
+        for (int32_t i = t; i < a.nbw; i += EP_TPB) ep_bits[i] = 0u;
+        __syncthreads();
+    }
+    ep_bitmap(a);
+    __syncthreads();
     if (c0 >= c1) return;
 
     uint32_t *qc = q_col[wv], *qe = q_ent[wv], *qo = q_ord[wv];
@@ -596,17 +596,24 @@ hipError_t launch_entry_auto(const DevMatrix &A, const DevCtx &C, int mode, cons
     }
 }
 
-hipError_t launch_entry_scatter(const DevMatrix &A, const DevCtx &C, int mode, int32_t k, const int32_t *x_idx,
+template <bool COUNT>
+static hipError_t entry_scatter(const DevMatrix &A, const DevCtx &C, int mode, int32_t k, const int32_t *x_idx,
                                 const void *x_val, hipStream_t s)
 {
-    if (k <= 0) return hipSuccess;
     const dim3 g((k + ES_TPB - 1) / ES_TPB), b(ES_TPB);
     switch (mode) {
-    case M_F32: hipLaunchKernelGGL(k_entry_scatter<M_F32>, g, b, 0, s, x_idx, x_val, k, A.n, C.xd, C.xmask, A.ce_ptr, C.items, C.counters); break;
-    case M_F16: hipLaunchKernelGGL(k_entry_scatter<M_F16>, g, b, 0, s, x_idx, x_val, k, A.n, C.xd, C.xmask, A.ce_ptr, C.items, C.counters); break;
-    default: hipLaunchKernelGGL(k_entry_scatter<M_BOOL>, g, b, 0, s, x_idx, x_val, k, A.n, C.xd, C.xmask, A.ce_ptr, C.items, C.counters); break;
+    case M_F32: hipLaunchKernelGGL((k_entry_scatter<M_F32, COUNT>), g, b, 0, s, x_idx, x_val, k, A.n, C.xd, C.xmask, A.ce_ptr, C.items, C.counters); break;
+    case M_F16: hipLaunchKernelGGL((k_entry_scatter<M_F16, COUNT>), g, b, 0, s, x_idx, x_val, k, A.n, C.xd, C.xmask, A.ce_ptr, C.items, C.counters); break;
+    default: hipLaunchKernelGGL((k_entry_scatter<M_BOOL, COUNT>), g, b, 0, s, x_idx, x_val, k, A.n, C.xd, C.xmask, A.ce_ptr, C.items, C.counters); break;
     }
     return hipGetLastError();
+}
+
+hipError_t launch_entry_scatter(const DevMatrix &A, const DevCtx &C, int mode, int32_t k, const int32_t *x_idx,
+                                const void *x_val, bool count, hipStream_t s)
+{
+    if (k <= 0) return hipSuccess;
+    return count ? entry_scatter<true>(A, C, mode, k, x_idx, x_val, s) : entry_scatter<false>(A, C, mode, k, x_idx, x_val, s);
 }
 
 hipError_t launch_entry_push(const DevMatrix &A, const DevCtx &C, int mode, const uint32_t *omask, int complement,

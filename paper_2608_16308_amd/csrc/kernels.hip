@@ -2732,6 +2732,8 @@ __global__ __launch_bounds__(FTPB) void k_finalize(uint32_t *__restrict__ ybits,
         counters[C_XPOP] = 0;
         counters[C_EITEMS] = 0;
         counters[C_EITEMS + 1] = 0;
+        counters[C_ECOUNT] = 0;
+        counters[C_ECOUNT + 1] = 0;
     }
     (void)m;
 }

@@ -134,7 +134,8 @@ enum Counter : int {
     C_XPOP = 9,      // distinct x indices (mask popcounts), summed by the scan tiles
     C_SYNCERR = 10,  // single launch: a bounded wait for other workgroups ran out
     C_EITEMS = 12,   // (64 bits) push items and tasks over the column-entry view (k_entry_scatter)
-    C_COUNT = 14
+    C_ECOUNT = 14,   // (64 bits) distinct x indices << 32 | nonzero vector blocks (k_entry_scatter)
+    C_COUNT = 16
 };
 constexpr int PATH_PUSH = 1, PATH_PULL = 2;
 #ifndef HV_CHUNK_BLOCKS
@@ -238,17 +239,19 @@ hipError_t launch_scan_dense(const DevMatrix &A, DevCtx &C, int mode, const void
 hipError_t launch_main(const DevMatrix &A, const DevCtx &C, int mode, const void *xd,
                        const uint32_t *omask, int complement, int32_t *parent, int forced_path,
                        hipStream_t s);
-// Traversals over the entry views (A.re_nchunk > 0), any mode but BFS.  None
-// of them writes the call's counters.
+// Traversals over the entry views (A.re_nchunk > 0), any mode but BFS.  The
+// blocker counts in C_XBAD, C_EITEMS and (count) C_ECOUNT, which the
+// compaction of y clears; the traversals write no counter.
 //   launch_entry_scatter  blocker that also lists push items (into C.items:
-//                         at most one per x index), as push and auto need
+//                         at most one per x index), as push and auto need;
+//                         count: and counts what the automatic choice asks for
 //   launch_entry_pull     pull; scanned: a scan ran, and the kernel returns
 //                         at once when its choice is push; dense_out: the y
 //                         structure is not wanted
 //   launch_entry_push     push
 //   launch_entry_auto     the choice is taken on the device
 hipError_t launch_entry_scatter(const DevMatrix &A, const DevCtx &C, int mode, int32_t k, const int32_t *x_idx,
-                                const void *x_val, hipStream_t s);
+                                const void *x_val, bool count, hipStream_t s);
 hipError_t launch_entry_pull(const DevMatrix &A, const DevCtx &C, int mode, const uint32_t *omask, int complement,
                              bool scanned, bool dense_out, hipStream_t s);
 hipError_t launch_entry_push(const DevMatrix &A, const DevCtx &C, int mode, const uint32_t *omask, int complement,
