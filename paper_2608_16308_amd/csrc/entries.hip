@@ -495,33 +495,12 @@ __global__ __launch_bounds__(EP_TPB) void k_entry_pull(EntryPullArgs a)
     }
 }
 
-// Resident workgroups of a kernel, cached per dynamic LDS size.
-template <auto KERNEL, int NTH>
-static int resident(size_t dyn)
-{
-    static size_t cached_lds[8];
-    static int cached_grid[8];
-    static int ncached = 0;
-    for (int i = 0; i < ncached; ++i)
-        if (cached_lds[i] == dyn) return cached_grid[i];
-    int dev = 0, cus = 0, per_cu = 0, grid = 256;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, KERNEL, NTH, dyn) == hipSuccess && cus > 0 && per_cu > 0)
-        grid = cus * per_cu;
-    if (ncached < 8) {
-        cached_lds[ncached] = dyn;
-        cached_grid[ncached] = grid;
-        ++ncached;
-    }
-    return grid;
-}
-
 template <int MODE, bool DECIDE>
 static hipError_t entry_pull(const EntryPullArgs &a, hipStream_t s)
 {
     const size_t dyn = (size_t)a.nbw * 4;
-    const int grid = std::max(1, std::min(resident<k_entry_pull<MODE, DECIDE>, EP_TPB>(dyn), (int)a.nchunk));
+    const int r = resident_workgroups((const void *)k_entry_pull<MODE, DECIDE>, EP_TPB, dyn);
+    const int grid = std::max(1, std::min(r > 0 ? r : 256, (int)a.nchunk));
     hipLaunchKernelGGL((k_entry_pull<MODE, DECIDE>), dim3(grid), dim3(EP_TPB), dyn, s, a);
     return hipGetLastError();
 }

@@ -42,6 +42,7 @@
 //  * wave scans and row reductions use DPP row shifts and broadcasts.
 #include <algorithm>
 #include <climits>
+#include <mutex>
 
 #include "device_common.hpp"
 #include "kernels.hpp"
@@ -3193,74 +3194,65 @@ static inline int grid_for(int64_t items, int per_block, int cap)
     return (int)g;
 }
 
-// Resident workgroups of a traversal kernel on the whole device (compute
-// units x workgroups per compute unit at its register and LDS use), so that
-// the persistent grid is exactly one round of residency.
+int resident_workgroups(const void *kernel, int threads, size_t dyn_lds)
+{
+    // (the kernels' grids use fewer than a hundred combinations in most
+    // programs; one that shares a place with another is asked for again)
+    struct Known {
+        const void *kernel;
+        size_t dyn_lds;
+        int dev, threads, blocks;
+    };
+    static Known known[512];
+    static std::mutex mu;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    uint64_t h = (uint64_t)(uintptr_t)kernel * 0x9E3779B97F4A7C15ull;
+    h = (h ^ (uint64_t)dyn_lds ^ (uint64_t)dev << 40) * 0x9E3779B97F4A7C15ull;
+    std::lock_guard<std::mutex> lock(mu);
+    Known &k = known[h >> 55];
+    if (k.kernel == kernel && k.dyn_lds == dyn_lds && k.dev == dev && k.threads == threads) return k.blocks;
+    int cus = 0, per_cu = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, dyn_lds) != hipSuccess || cus <= 0 ||
+        per_cu <= 0) {
+        (void)hipGetLastError();  // (the launch that follows does not report it)
+        return 0;
+    }
+    k = Known{kernel, dyn_lds, dev, threads, cus * per_cu};
+    return k.blocks;
+}
+
+// Resident workgroups of a traversal kernel, so that the persistent grid is
+// exactly one round of residency.
 template <int MODE, int PATH>
 static int resident_grid(size_t dyn_lds)
 {
-    // cached per dynamic LDS size (a handful of distinct sizes occur)
-    static size_t cached_lds[8];
-    static int cached_grid[8];
-    static int ncached = 0;
-    for (int i = 0; i < ncached; ++i)
-        if (cached_lds[i] == dyn_lds) return cached_grid[i];
-    int dev = 0, cus = 0, per_cu = 0, grid = MAX_MAIN_GRID;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_traverse<MODE, PATH>, TPB, dyn_lds) == hipSuccess &&
-        cus > 0 && per_cu > 0)
-        grid = cus * per_cu;
-    if (ncached < 8) {
-        cached_lds[ncached] = dyn_lds;
-        cached_grid[ncached] = grid;
-        ++ncached;
-    }
-    return grid;
+    const int r = resident_workgroups((const void *)k_traverse<MODE, PATH>, TPB, dyn_lds);
+    return r > 0 ? r : MAX_MAIN_GRID;
 }
 
 // Resident workgroups of k_pull_compact with dyn_lds bytes of dynamic LDS.
 template <int MODE>
 static int compact_grid(size_t dyn_lds)
 {
-    static size_t cached_lds[8];
-    static int cached_grid[8];
-    static int ncached = 0;
-    for (int i = 0; i < ncached; ++i)
-        if (cached_lds[i] == dyn_lds) return cached_grid[i];
-    int dev = 0, cus = 0, per_cu = 0, grid = MAX_MAIN_GRID;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_pull_compact<MODE>, TPB, dyn_lds) == hipSuccess &&
-        cus > 0 && per_cu > 0)
-        grid = min(cus * per_cu, MAX_MAIN_GRID);
-    if (ncached < 8) {
-        cached_lds[ncached] = dyn_lds;
-        cached_grid[ncached] = grid;
-        ++ncached;
-    }
-    return grid;
+    const int r = resident_workgroups((const void *)k_pull_compact<MODE>, TPB, dyn_lds);
+    return r > 0 ? min(r, MAX_MAIN_GRID) : MAX_MAIN_GRID;
 }
 
-// Chunks per round for k_rows: the fewest (at most 16) that keep its grid
-// within one round of resident workgroups.
+// Chunks per round of a kernel that holds `resident` workgroups: the fewest
+// (at most 16) that keep its grid within one round of them.
+static int32_t chunks_per_round(int64_t nchunk, int resident)
+{
+    if (resident <= 0) return TPB / 16;
+    const int64_t c = (nchunk + resident - 1) / resident;
+    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(c, TPB / 16));
+}
+
 template <int MODE, int NB>
 static int32_t rows_cpw(int64_t nchunk, size_t dyn)
 {
-    static int resident[2] = {0, 0};
-    const int slot = dyn ? 1 : 0;
-    if (resident[slot] == 0) {
-        int dev = 0, cus = 0, per_cu = 0;
-        resident[slot] = -1;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_rows<MODE, NB>, TPB, dyn) == hipSuccess &&
-            cus > 0 && per_cu > 0)
-            resident[slot] = cus * per_cu;
-    }
-    if (resident[slot] <= 0) return TPB / 16;
-    const int64_t c = (nchunk + resident[slot] - 1) / resident[slot];
-    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(c, TPB / 16));
+    return chunks_per_round(nchunk, resident_workgroups((const void *)k_rows<MODE, NB>, TPB, dyn));
 }
 
 // Launch order: the pull kernel (and k_pull_compact when the bitmap does not
@@ -3460,24 +3452,8 @@ bool fused_fits(const DevMatrix &A, int32_t k)
 template <int MODE>
 static int fused_grid(size_t dyn_lds)
 {
-    static size_t cached_lds[8];
-    static int cached_grid[8];
-    static int ncached = 0;
-    for (int i = 0; i < ncached; ++i)
-        if (cached_lds[i] == dyn_lds) return cached_grid[i];
-    int dev = 0, cus = 0, per_cu = 0, grid = 256;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_fused<MODE>, TPB, dyn_lds) == hipSuccess &&
-        cus > 0 && per_cu > 0)
-        grid = cus * per_cu;
-    if (grid > FUSED_MAX_GRID) grid = FUSED_MAX_GRID;
-    if (ncached < 8) {
-        cached_lds[ncached] = dyn_lds;
-        cached_grid[ncached] = grid;
-        ++ncached;
-    }
-    return grid;
+    const int r = resident_workgroups((const void *)k_fused<MODE>, TPB, dyn_lds);
+    return min(r > 0 ? r : 256, FUSED_MAX_GRID);
 }
 
 hipError_t launch_fused(const DevMatrix &A, DevCtx &C, int mode, int32_t k, const int32_t *x_idx,
@@ -3574,34 +3550,10 @@ bool rows_dx_fits(const DevMatrix &A, const void *x_dense)
     return A.nblk > 0 && A.nheavy == A.nblk && scan_takes_dense(A, x_dense) && A.nbc <= ROWS_DX_MAX_NBC;
 }
 
-// Chunks per round for k_rows_dx (as rows_cpw), its residency cached per
-// dynamic LDS size.
 template <int MODE>
 static int32_t rows_dx_cpw(int64_t nchunk, size_t dyn)
 {
-    static size_t cached_lds[8];
-    static int cached_res[8];
-    static int ncached = 0;
-    int res = -1;
-    for (int i = 0; i < ncached; ++i)
-        if (cached_lds[i] == dyn) res = cached_res[i];
-    if (res < 0) {
-        int dev = 0, cus = 0, per_cu = 0;
-        res = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_rows_dx<MODE>, TPB, dyn) == hipSuccess &&
-            cus > 0 && per_cu > 0)
-            res = cus * per_cu;
-        if (ncached < 8) {
-            cached_lds[ncached] = dyn;
-            cached_res[ncached] = res;
-            ++ncached;
-        }
-    }
-    if (res <= 0) return TPB / 16;
-    const int64_t c = (nchunk + res - 1) / res;
-    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(c, TPB / 16));
+    return chunks_per_round(nchunk, resident_workgroups((const void *)k_rows_dx<MODE>, TPB, dyn));
 }
 
 hipError_t launch_rows_dx(const DevMatrix &A, const DevCtx &C, int mode, const void *x_dense, void *y,

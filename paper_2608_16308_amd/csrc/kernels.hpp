@@ -204,6 +204,10 @@ int32_t compact_list_regions();
 
 enum Mode : int { M_F32 = 0, M_F16 = 1, M_BOOL = 2, M_BFS = 3 };
 
+// Workgroups of `kernel` (threads wide, dyn_lds bytes of dynamic LDS) that the
+// current device holds at once, or 0 if it cannot be asked.  Any thread may
+// call it; answers are kept per device, kernel and LDS size.
+int resident_workgroups(const void *kernel, int threads, size_t dyn_lds);
 hipError_t launch_scatter(const DevMatrix &A, const DevCtx &C, int mode, int32_t k,
                           const int32_t *x_idx, const void *x_val, hipStream_t s);
 hipError_t launch_ballot(const DevMatrix &A, const DevCtx &C, int mode, const void *x_dense,
