@@ -18,6 +18,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <mutex>
 #include <new>
 #include <thread>
@@ -35,7 +36,11 @@ dbs_status dbs_fail(dbs_status st, const char *fmt, ...)
     va_start(ap, fmt);
     vsnprintf(buf, sizeof(buf), fmt, ap);
     va_end(ap);
-    g_last_error = buf;
+    try {
+        g_last_error = buf;
+    } catch (const std::bad_alloc &) {
+        g_last_error.clear();
+    }
     return st;
 }
 
@@ -80,17 +85,35 @@ void parallel_chunks(int64_t n, int64_t chunk, F &&f)
         return;
     }
     std::atomic<int64_t> next{0};
-    std::vector<std::thread> pool;
-    for (int t = 0; t < nt; ++t) {
-        pool.emplace_back([&, t]() {
+    std::exception_ptr error;
+    std::mutex mu;
+    auto work = [&](int t) {
+        try {
             for (;;) {
                 int64_t s = next.fetch_add(chunk);
                 if (s >= n) break;
                 f(t, s, std::min(n, s + chunk));
             }
-        });
+        } catch (...) {
+            // (an exception may not leave a thread: the first one is rethrown
+            // to the caller when all have stopped)
+            std::lock_guard<std::mutex> g(mu);
+            if (!error) error = std::current_exception();
+            next.store(n);
+        }
+    };
+    std::vector<std::thread> pool;
+    pool.reserve((size_t)nt);
+    for (int t = 1; t < nt; ++t) {
+        try {
+            pool.emplace_back(work, t);
+        } catch (...) {
+            break;  // fewer threads, if no more can be had
+        }
     }
+    work(0);
     for (auto &th : pool) th.join();
+    if (error) std::rethrow_exception(error);
 }
 
 struct Failure {
@@ -309,6 +332,16 @@ void build_row_entries(dbs_host_matrix *h, const int64_t *row_ptr, const int32_t
     });
 }
 
+void drop_row_entries(dbs_host_matrix *h)
+{
+    h->nre_chunk = 0;
+    h->re_col.reset();
+    h->re_val.reset();
+    h->re_row = {};
+    h->re_chord = {};
+    h->re_info = {};
+}
+
 struct RowBlockSizes {
     int64_t nblk = 0, bytes = 0, nseg = 0;
 };
@@ -521,7 +554,13 @@ extern "C" dbs_status dbs_host_build_csr(int32_t m, int32_t n, int64_t nnz, cons
         int64_t ncoo = 0;
         for (const int64_t c : tcoo) ncoo += c;
         h->re_sparse = entries_sparse(nnz, ncoo, o.force_type);
-        if (entries_wanted(nnz, h->re_sparse, vt, o.force_type)) build_row_entries(h, row_ptr, col_idx, vals, vb);
+        if (entries_wanted(nnz, h->re_sparse, vt, o.force_type)) {
+            try {
+                build_row_entries(h, row_ptr, col_idx, vals, vb);
+            } catch (const std::bad_alloc &) {
+                drop_row_entries(h);  // (every call has a way without the view)
+            }
+        }
 
         // ---- block-CSC view by a counting sort over blocks ----
         const int32_t nbc = h->nbc;

@@ -239,3 +239,15 @@ def test_basic_baseline_checks_input_before_any_device_call():
         with pytest.raises(dbs.DbsError) as e:
             dbs.BasicMatrix(a.m, a.n, a.row_ptr, a.col_idx, a.vals)
         assert e.value.status == _lib.DBS_ERR_DEVICE
+
+
+def test_host_allocations_that_fail(tmp_path):
+    """Every host allocation of a build failing in turn, on threads too: see
+    native/builder_alloc_check.cpp."""
+    import os
+    import subprocess
+    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "native", "builder_alloc_check.cpp")
+    exe = str(tmp_path / "check")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-pthread", "-o", exe, src], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
