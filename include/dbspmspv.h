@@ -125,7 +125,9 @@ typedef struct {
     int64_t nseg;               /* pull segments */
     int64_t blocks_by_type[DBS_NUM_BLOCK_TYPES];
     int64_t payload_bytes;      /* low-level block payload */
-    int64_t db_bytes;           /* every array of the format (views, metadata, payload, segments) */
+    int64_t db_bytes;           /* every array of the format (block views, metadata, payload, segments);
+                                   what a device matrix may carry besides is not in it, see
+                                   dbs_matrix_upload */
     int64_t csr_bytes;          /* plain CSR of the same matrix: (v + 4) nnz + 4 (m + 1) */
     int64_t csr_csc_bytes;      /* CSR plus CSC: csr_bytes + (v + 4) nnz + 4 (n + 1) */
 } dbs_matrix_info;
@@ -208,7 +210,15 @@ dbs_status dbs_storage_model(int64_t rows, int64_t cols, int64_t nnz, int32_t va
 /* ---------------------------------------------------------------------- */
 
 /* Copies a host-side DB matrix to the current device (one upload).
- * DBS_ERR_UNSUPPORTED for more than 2^26 block columns (n > 2^30).          */
+ * DBS_ERR_UNSUPPORTED for more than 2^26 block columns (n > 2^30).
+ * Besides the format's arrays the device matrix carries, where they help,
+ *   entry views   (at least half of the entries in COO blocks, or a pattern; no
+ *                 forced block format): the entries by rows and by columns,
+ *                 8 + 2 V bytes per entry (V: bytes of a value), 4 per column
+ *                 and up to 12 per row
+ *   a block list  (valued, eight entries per block and more): 12 bytes per block
+ * Without the memory for them they are left out, and calls take their way over
+ * the blocks: the same results, more slowly.                               */
 dbs_status dbs_matrix_upload(const dbs_host_matrix *h, dbs_matrix **out);
 
 /* dbs_host_build_csr + dbs_matrix_upload + dbs_host_destroy. */

@@ -18,11 +18,6 @@ using namespace dbs;
 
 namespace {
 
-dbs_status hip_fail(hipError_t e, const char *what)
-{
-    return dbs_fail(DBS_ERR_DEVICE, "%s: %s", what, hipGetErrorString(e));
-}
-
 #define HIP_TRY(expr, what)                          \
     do {                                             \
         hipError_t e_ = (expr);                      \
@@ -230,6 +225,58 @@ dbs_status column_entries(dbs_matrix *A)
     return DBS_OK;
 }
 
+// The entry views of a host matrix that has them.
+static dbs_status upload_entries(const dbs_host_matrix *h, dbs_matrix *A)
+{
+    DevMatrix &d = A->d;
+    const size_t ncol = (size_t)h->nre_chunk * RE_CHUNK, vbytes = (size_t)h->nnz * dtype_bytes(h->dtype);
+    const uint8_t *rv = nullptr;
+    const uint64_t *ri = nullptr;
+    dbs_status st;
+    if ((st = dev_upload(A->allocs, h->re_col.get(), ncol, &d.re_col, 64)) != DBS_OK ||
+        (st = dev_upload(A->allocs, h->re_val.get(), vbytes, &rv)) != DBS_OK ||
+        (st = dev_upload(A->allocs, h->re_row, &d.re_row)) != DBS_OK ||
+        (st = dev_upload(A->allocs, h->re_chord, &d.re_chord)) != DBS_OK ||
+        (!h->re_info.empty() && (st = dev_upload(A->allocs, h->re_info, &ri)) != DBS_OK))
+        return st;
+    d.re_val = rv;
+    d.re_sparse = h->re_sparse;
+    d.re_info = (const int2 *)ri;
+    d.re_nnz = (int32_t)h->nnz;
+    d.re_nchunk = (int32_t)h->nre_chunk;
+    return column_entries(A);
+}
+
+// The block list of the matrix-core pass.
+static dbs_status upload_block_list(const dbs_host_matrix *h, dbs_matrix *A)
+{
+    std::vector<int32_t> col, ptr;
+    std::vector<uint64_t> desc;
+    try {
+        col.resize((size_t)h->nblk);
+        desc.resize((size_t)h->nblk);
+        ptr.assign((size_t)h->nbr * MC_COUNT + 1, 0);
+    } catch (const std::bad_alloc &) {
+        return dbs_fail(DBS_ERR_ALLOC, "host allocation failed during upload");
+    }
+    for (int32_t R = 0; R < h->nbr; ++R) {
+        int32_t *at = ptr.data() + (size_t)R * MC_COUNT, cnt[MC_COUNT] = {0, 0, 0, 0};
+        for (int32_t b = h->rb_ptr[R]; b < h->rb_ptr[R + 1]; ++b)
+            ++cnt[mfma_class(desc_type(h->desc[b]), desc_nnz(h->desc[b]))];
+        for (int k = 0; k < MC_COUNT; ++k) at[k + 1] = at[k] + cnt[k];
+        int32_t to[MC_COUNT] = {at[0], at[1], at[2], at[3]};
+        for (int32_t b = h->rb_ptr[R]; b < h->rb_ptr[R + 1]; ++b) {
+            const int32_t q = to[mfma_class(desc_type(h->desc[b]), desc_nnz(h->desc[b]))]++;
+            col[(size_t)q] = h->cb_col[b];
+            desc[(size_t)q] = h->desc[b];
+        }
+    }
+    const dbs_status st = dev_upload(A->allocs, col, &A->d.ab_col);
+    if (st != DBS_OK) return st;
+    const dbs_status st2 = dev_upload(A->allocs, desc, &A->d.ab_desc);
+    return st2 != DBS_OK ? st2 : dev_upload(A->allocs, ptr, &A->d.ab_rptr);
+}
+
 extern "C" dbs_status dbs_matrix_upload(const dbs_host_matrix *h, dbs_matrix **out)
 {
     if (!h || !out) return dbs_fail(DBS_ERR_ARG, "dbs_matrix_upload: NULL argument");
@@ -254,6 +301,7 @@ extern "C" dbs_status dbs_matrix_upload(const dbs_host_matrix *h, dbs_matrix **o
     std::vector<uint32_t> seg_rs;
     std::vector<int32_t> task_order;
     try {
+        A->allocs.reserve(32);
         const size_t nslots = (size_t)16 * (size_t)h->nseg;
         sl_col.assign(nslots, -1);
         sl_desc.assign(nslots, 0ull);
@@ -329,67 +377,13 @@ extern "C" dbs_status dbs_matrix_upload(const dbs_host_matrix *h, dbs_matrix **o
         delete A;
         return s2;
     }
-    if (h->nre_chunk > 0) {
-        const size_t ncol = (size_t)h->nre_chunk * RE_CHUNK, vbytes = (size_t)h->nnz * dtype_bytes(h->dtype);
-        const uint8_t *rv = nullptr;
-        if ((s2 = dev_upload(A->allocs, h->re_col.get(), ncol, &d.re_col, 64)) != DBS_OK ||
-            (s2 = dev_upload(A->allocs, h->re_val.get(), vbytes, &rv)) != DBS_OK ||
-            (s2 = dev_upload(A->allocs, h->re_row, &d.re_row)) != DBS_OK ||
-            (s2 = dev_upload(A->allocs, h->re_chord, &d.re_chord)) != DBS_OK) {
-            free_all(A->allocs);
-            delete A;
-            return s2;
-        }
-        d.re_val = rv;
-        d.re_sparse = h->re_sparse;
-        if (!h->re_info.empty()) {
-            const uint64_t *ri = nullptr;
-            if ((s2 = dev_upload(A->allocs, h->re_info, &ri)) != DBS_OK) {
-                free_all(A->allocs);
-                delete A;
-                return s2;
-            }
-            d.re_info = (const int2 *)ri;
-        }
-        d.re_nnz = (int32_t)h->nnz;
-        d.re_nchunk = (int32_t)h->nre_chunk;
-        if ((s2 = column_entries(A)) != DBS_OK) {
-            free_all(A->allocs);
-            delete A;
-            return s2;
-        }
-    }
-    if (h->nblk > 0 && h->dtype != DBS_PATTERN && h->nnz >= BLOCK_LIST_ENTRIES * h->nblk) {
-        std::vector<int32_t> col, ptr;
-        std::vector<uint64_t> desc;
-        try {
-            col.resize((size_t)h->nblk);
-            desc.resize((size_t)h->nblk);
-            ptr.assign((size_t)h->nbr * MC_COUNT + 1, 0);
-            for (int32_t R = 0; R < h->nbr; ++R) {
-                int32_t *at = ptr.data() + (size_t)R * MC_COUNT, cnt[MC_COUNT] = {0, 0, 0, 0};
-                for (int32_t b = h->rb_ptr[R]; b < h->rb_ptr[R + 1]; ++b)
-                    ++cnt[mfma_class(desc_type(h->desc[b]), desc_nnz(h->desc[b]))];
-                for (int k = 0; k < MC_COUNT; ++k) at[k + 1] = at[k] + cnt[k];
-                int32_t to[MC_COUNT] = {at[0], at[1], at[2], at[3]};
-                for (int32_t b = h->rb_ptr[R]; b < h->rb_ptr[R + 1]; ++b) {
-                    const int32_t q = to[mfma_class(desc_type(h->desc[b]), desc_nnz(h->desc[b]))]++;
-                    col[(size_t)q] = h->cb_col[b];
-                    desc[(size_t)q] = h->desc[b];
-                }
-            }
-        } catch (const std::bad_alloc &) {
-            free_all(A->allocs);
-            delete A;
-            return dbs_fail(DBS_ERR_ALLOC, "host allocation failed during upload");
-        }
-        if ((s2 = dev_upload(A->allocs, col, &d.ab_col)) != DBS_OK ||
-            (s2 = dev_upload(A->allocs, desc, &d.ab_desc)) != DBS_OK ||
-            (s2 = dev_upload(A->allocs, ptr, &d.ab_rptr)) != DBS_OK) {
-            free_all(A->allocs);
-            delete A;
-            return s2;
-        }
+    if (h->nre_chunk > 0) s2 = optional_arrays(A, [&] { return upload_entries(h, A); });
+    if (s2 == DBS_OK && h->nblk > 0 && h->dtype != DBS_PATTERN && h->nnz >= BLOCK_LIST_ENTRIES * h->nblk)
+        s2 = optional_arrays(A, [&] { return upload_block_list(h, A); });
+    if (s2 != DBS_OK) {
+        free_all(A->allocs);
+        delete A;
+        return s2;
     }
     d.nheavy = (int64_t)hv_col.size();
     d.nchunk = (int64_t)hv_crow.size();

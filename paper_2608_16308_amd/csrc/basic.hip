@@ -101,6 +101,7 @@ __global__ __launch_bounds__(BTPB) void k_basic_push(const int64_t *__restrict__
 
 dbs_status basic_hip_fail(hipError_t e, const char *what)
 {
+    (void)hipGetLastError();  // (or the next launch reports it)
     return dbs_fail(DBS_ERR_DEVICE, "%s: %s", what, hipGetErrorString(e));
 }
 

@@ -35,14 +35,10 @@ constexpr int CTPB = 256;             // 4 waves per workgroup, one tile each
 constexpr int RS = 11;                // per-row statistics, see k_conv_rows
 constexpr int PRE = 5;                // per-row prefixes: blocks, bytes, segments, non-COO, chunks
 
-dbs_status conv_fail(hipError_t e, const char *what)
-{
-    return dbs_fail(DBS_ERR_DEVICE, "%s: %s", what, hipGetErrorString(e));
-}
 #define CONV_TRY(expr, what)                             \
     do {                                                 \
         hipError_t e_ = (expr);                          \
-        if (e_ != hipSuccess) return conv_fail(e_, what); \
+        if (e_ != hipSuccess) return hip_fail(e_, what); \
     } while (0)
 
 // Raw bits of element (row, col) of the dense input (0 outside the matrix).
@@ -524,8 +520,8 @@ dbs_status row_entries(int32_t m, int32_t n, const void *w, int64_t ld, int64_t 
 }
 
 template <int VB>
-dbs_status convert(int32_t m, int32_t n, const void *d_w, int64_t ld, const dbs_build_opts &o, hipStream_t s,
-                   dbs_matrix *A)
+dbs_status convert(int32_t m, int32_t n, const void *d_w, int64_t ld, const dbs_build_opts &o, bool optional,
+                   hipStream_t s, dbs_matrix *A)
 {
     DevMatrix &d = A->d;
     const int32_t nbr = (int32_t)(((int64_t)m + BS - 1) / BS), nbc = (int32_t)(((int64_t)n + BS - 1) / BS);
@@ -604,7 +600,7 @@ dbs_status convert(int32_t m, int32_t n, const void *d_w, int64_t ld, const dbs_
         (st = conv_alloc(A->allocs, (size_t)bytes, &pay, 0, s, PAYLOAD_PAD)) != DBS_OK)
         return st;
     CONV_TRY(scratch((size_t)nblk * 8, (void **)&blk_desc), "hipMalloc (descriptors)");
-    const bool list = nblk > 0 && nnz >= BLOCK_LIST_ENTRIES * nblk;
+    const bool list = optional && nblk > 0 && nnz >= BLOCK_LIST_ENTRIES * nblk;
     int32_t *ab_col = nullptr, *ab_rptr = nullptr, *blk_col = nullptr;
     uint64_t *ab_desc = nullptr;
     if (list) {
@@ -674,7 +670,7 @@ dbs_status convert(int32_t m, int32_t n, const void *d_w, int64_t ld, const dbs_
     d.hv_cstart = hv_cstart;
     d.hv_crow = hv_crow;
     d.hv_rowchunks = hv_rowchunks;
-    if (entries_wanted(nnz, entries_sparse(nnz, coo, o.force_type), d.dtype, o.force_type)) {
+    if (optional && entries_wanted(nnz, entries_sparse(nnz, coo, o.force_type), d.dtype, o.force_type)) {
         const dbs_status es = row_entries<VB>(m, n, d_w, ld, nnz, s, A);
         if (es != DBS_OK) return es;
     }
@@ -722,17 +718,30 @@ extern "C" dbs_status dbs_matrix_build_dense(int32_t m, int32_t n, const void *d
         return dbs_fail(DBS_ERR_ARG, "invalid build options");
     int cnt = 0;
     if (hipGetDeviceCount(&cnt) != hipSuccess || cnt <= 0) return dbs_fail(DBS_ERR_DEVICE, "no HIP device available");
-    dbs_matrix *A = new (std::nothrow) dbs_matrix();
-    if (!A) return dbs_fail(DBS_ERR_ALLOC, "host allocation failed");
-    A->d.dtype = (int32_t)vt;
     const hipStream_t s = (hipStream_t)stream;
-    dbs_status st = vt == DBS_F32 ? convert<4>(m, n, d_w, ld, o, s, A) : convert<2>(m, n, d_w, ld, o, s, A);
-    if (st != DBS_OK) {
+    // the entry views and the block list are optional: without the memory for
+    // them, once more without them
+    for (bool optional : {true, false}) {
+        dbs_matrix *A = new (std::nothrow) dbs_matrix();
+        if (!A) return dbs_fail(DBS_ERR_ALLOC, "host allocation failed");
+        A->d.dtype = (int32_t)vt;
+        dbs_status st;
+        try {
+            A->allocs.reserve(32);
+            st = vt == DBS_F32 ? convert<4>(m, n, d_w, ld, o, optional, s, A)
+                               : convert<2>(m, n, d_w, ld, o, optional, s, A);
+        } catch (const std::bad_alloc &) {
+            st = dbs_fail(DBS_ERR_ALLOC, "host allocation failed during the conversion");
+        }
+        if (st == DBS_OK) {
+            *out = A;
+            return DBS_OK;
+        }
         (void)hipStreamSynchronize(s);
+        const bool again = optional && out_of_memory(st);
         for (void *p : A->allocs) (void)hipFree(p);
         delete A;
-        return st;
+        if (!again) return st;
     }
-    *out = A;
-    return DBS_OK;
+    return DBS_ERR_ALLOC;  // (not reached)
 }

@@ -69,3 +69,78 @@ for t in threads: t.start()
 for t in threads: t.join()
 assert not wrong, wrong
 """)
+
+
+ALLOCS = MATRIX + """
+allocs, frees = var("fake_allocs"), var("fake_frees")
+fail_at, fail_from = var("fake_fail_at"), var("fake_fail_from")
+
+def failing(make, at=-1, frm=-1):
+    '''(status, allocations, of them not freed) of make(out) with failures'''
+    out = ctypes.c_void_p()
+    allocs.value = frees.value = 0
+    fail_at.value, fail_from.value = at, frm
+    st = make(out)
+    fail_at.value = fail_from.value = -1
+    n = allocs.value
+    failed = 0 if at < 0 and frm < 0 else 1 if at >= 0 and n > at else max(0, n - frm) if frm >= 0 else 0
+    left = n - failed - frees.value
+    if st == 0:
+        lib.dbs_matrix_destroy(out)
+        return st, n, n - failed - frees.value, left
+    assert not out.value
+    return st, n, left, left
+"""
+
+
+def test_upload_without_memory_for_the_views():
+    """Every device allocation of an upload failing in turn: the entry views
+    and the block list are left out, the format's own arrays are required;
+    nothing leaks, and the matrix works."""
+    fake_hip.run(ALLOCS + """
+def upload(hm):
+    return lambda out: lib.dbs_matrix_upload(hm._h, ctypes.byref(out))
+host = lambda args, **o: dbs.HostMatrix.from_csr(*args, dbs.default_opts(**o))
+rng = np.random.default_rng(1)
+r, c = np.nonzero(rng.random((64, 64)) < 0.4)
+filled = (64, 64, np.concatenate([[0], np.cumsum(np.bincount(r, minlength=64))]).astype(np.int64), c.astype(np.int32),
+          np.ones(r.size, np.float32))
+few = list_matrix(300, 300, 4)
+_, base, _, _ = failing(upload(host(few, force_type=0)))      # (a forced format has no views)
+for name, hm, more in (("views", host(few), True), ("pattern", host(list_matrix(300, 300, 4, None)), True),
+                       ("list", host(filled), True), ("neither", host(few, force_type=0), False)):
+    st, n, leak, kept = failing(upload(hm))
+    assert st == 0 and leak == 0 and (n > base) == more, (name, n, base)
+    for k in range(n):
+        st, _, leak, kept = failing(upload(hm), at=k)
+        assert leak == 0, (name, k, leak)
+        assert (st == 0) == (k >= base), (name, k, base, st)
+        if st == 0: assert kept < n, (name, k)
+        st, _, leak, kept = failing(upload(hm), frm=k)
+        assert leak == 0 and (st == 0) == (k >= base), (name, k, st)
+# a matrix without views takes the scan and the block traversals: a launch more
+full = Call(*few)
+full.pull()
+launches = var("fake_launches")
+launches.value = 0; full.pull(); with_views = launches.value
+fail_at.value = allocs.value + base
+bare = Call(*few)
+launches.value = 0; bare.pull()
+assert launches.value > with_views, (launches.value, with_views)
+""")
+
+
+def test_conversion_without_memory_for_the_views():
+    """Device allocations of dbs_matrix_build_dense: one that fails has it
+    start once more without the optional arrays; none leaks."""
+    fake_hip.run(ALLOCS + """
+w = np.ones((100, 200), np.float32)
+make = lambda out: lib.dbs_matrix_build_dense(100, 200, P(w), 200, 0, None, None, ctypes.byref(out))
+st, n, leak, _ = failing(make)
+assert st == 0 and leak == 0 and n > 10
+for k in range(n):
+    st, _, leak, _ = failing(make, at=k)
+    assert st == 0 and leak == 0, (k, st, leak)
+    st, _, leak, _ = failing(make, frm=k)
+    assert st != 0 and leak == 0, (k, st, leak)
+""")
