@@ -902,10 +902,19 @@ extern "C" dbs_status dbs_spmm_dense(dbs_ctx *ctx, const dbs_matrix *A, int32_t 
     if (!ctx->xdb && (!mfma || stats || rows_mfma_parts(A->d) > 1)) {
         const size_t xb = (size_t)DBS_MAX_BATCH * BS * ctx->max_nbc * 4;
         const size_t yb = (size_t)DBS_MAX_BATCH * BS * ctx->max_nbr * sizeof(double);
-        HIP_TRY(hipMalloc(&ctx->xdb, xb), "hipMalloc (batched x)");
-        HIP_TRY(hipMemset(ctx->xdb, 0, xb), "hipMemset (batched x)");
-        HIP_TRY(hipMalloc((void **)&ctx->yaccb, yb), "hipMalloc (batched y)");
-        HIP_TRY(hipMemset(ctx->yaccb, 0, yb), "hipMemset (batched y)");
+        // (both or neither: a later call finds them by xdb)
+        void *px = nullptr, *py = nullptr;
+        HIP_TRY(hipMalloc(&px, xb), "hipMalloc (batched x)");
+        hipError_t e = hipMalloc(&py, yb);
+        if (e == hipSuccess) e = hipMemset(px, 0, xb);
+        if (e == hipSuccess) e = hipMemset(py, 0, yb);
+        if (e != hipSuccess) {
+            (void)hipFree(px);
+            if (py) (void)hipFree(py);
+            return hip_fail(e, "hipMalloc (batched y)");
+        }
+        ctx->xdb = px;
+        ctx->yaccb = (double *)py;
     }
     const int32_t NB = nb <= 2 ? 2 : nb <= 4 ? 4 : 8;
     const hipStream_t s = ctx->stream;

@@ -144,3 +144,26 @@ for k in range(n):
     st, _, leak, _ = failing(make, frm=k)
     assert st != 0 and leak == 0, (k, st, leak)
 """)
+
+
+def test_batch_scratch_that_could_not_be_had():
+    """The second of the two batched buffers failing: the call reports it, the
+    next one allocates both."""
+    fake_hip.run(ALLOCS + """
+rng = np.random.default_rng(2)
+rows = np.repeat(np.arange(16), 2048)
+cols = np.tile(np.arange(2048), 16)
+rp = (np.arange(17) * 2048).astype(np.int64)
+c = Call(16, 2048, rp, cols.astype(np.int32), np.ones(rows.size, np.float32))   # (a block row in parts)
+x, y = np.ones((8, 2048), np.float32), np.zeros((8, 16), np.float32)
+spmm = lambda: lib.dbs_spmm_dense(c.ctx, c.A._h, 8, P(x), P(y), None, None)
+allocs.value = frees.value = 0
+fail_at.value = 1
+assert spmm() != 0
+assert allocs.value == 2 and frees.value == 1
+fail_at.value = -1
+allocs.value = 0
+assert spmm() == 0 and allocs.value == 2
+allocs.value = 0
+assert spmm() == 0 and allocs.value == 0
+""")
