@@ -85,7 +85,10 @@ typedef enum { DBS_PATH_AUTO = 0, DBS_PATH_PUSH = 1, DBS_PATH_PULL = 2 } dbs_pat
 /* The same rule for matrices that carry entry views (pattern matrices and
  * matrices of short COO blocks built from CSR on the host, no forced block
  * format): push iff the frontier's columns hold fewer entries than this share
- * of the matrix's.                                                        */
+ * of the matrix's, or fewer than five times the share while they are fewer
+ * than the entries of the vertices not reached and than four times those of
+ * the level before; and pull in any case behind a pull level that found more
+ * vertices than its workgroups could list as push items.                  */
 #define DBS_BFS_PUSH_ENTRIES 0.02f
 
 /* Low-level block formats (Sec. 3.2.1). */
@@ -338,8 +341,9 @@ typedef struct {
  *   d_y_val            capacity m values of A's dtype (NULL for DBS_OR_AND)
  *   d_y_nnz            one int32: nnz(y)
  *   stats              NULL, or filled after a stream synchronization
- * PATTERN matrices accept only DBS_OR_AND.  Values are accumulated in fp32
- * within a block segment and in fp64 across segments, then rounded once.
+ * PATTERN matrices accept only DBS_OR_AND.  Values are rounded once, from
+ * fp64 sums: of exact products on a matrix that carries entry views (see
+ * dbs_matrix_upload), else of sums in fp32 within a block segment.
  * Out-of-range or duplicate x indices are not detected on the host; they are
  * skipped / flagged on the device and reported through stats.             */
 dbs_status dbs_spmspv(dbs_ctx *ctx, const dbs_matrix *A, dbs_semiring sr, int32_t x_nnz,
@@ -439,7 +443,9 @@ typedef struct {
  * others as visited from the start (no edge reaches them), so that pull
  * levels skip their block rows sooner; the results are the same.  A matrix
  * that carries entry views (DBS_BFS_PUSH_ENTRIES) runs one kernel per level
- * over them, bottom-up rows ending at their first parent.
+ * over them, bottom-up rows ending at their first parent; its scratch (32
+ * bytes per column and four bitmaps) is allocated with a context sized by a
+ * pattern matrix, else by the context's first such call.
  *   d_level[n]   level of each vertex, -1 if unreachable, level[source] = 0
  *   d_parent[n]  smallest-id vertex of the previous level with an edge to v;
  *                parent[source] = source; -1 if unreachable

@@ -56,7 +56,7 @@ struct BfsArgs {
     int32_t policy;     // 0 auto, else PATH_PUSH / PATH_PULL
     double th3n;        // > 0: push iff nonzero vector blocks < th3n
     int64_t nnz;
-    int64_t push_max;   // else the entries of a frontier that pushes whatever the rest (see k_bfs_level)
+    int64_t push_max;   // else the entries of a frontier that pushes whatever the rest, if it is listed (k_bfs_level)
 };
 
 struct BfsLds {
@@ -136,7 +136,7 @@ __device__ __forceinline__ bool bfs_stream(const BfsArgs &a, const BfsCount &c)
     return a.stream && mf * 64 < a.nnz;
 }
 
-// Eight consecutive column words from a 4-byte aligned place.
+// Four consecutive column words from a 4-byte aligned place.
 struct __attribute__((packed, aligned(4))) Cols4 {
     uint32_t c[4];
 };
@@ -159,6 +159,10 @@ __global__ __launch_bounds__(BL_TPB, 8) void k_bfs_level(BfsArgs a, int32_t l)
     const bool lead = blockIdx.x == 0 && t == 0;
     if (lead) a.cnt[(l + 2) % 3] = BfsCount{};
     if (found == 0) return;  // the BFS has ended
+    // The automatic rule was found on R-MAT 22 and a stencil of 207,360 rows
+    // (a push of under 2% of the entries only: the stencil's fronts then pull,
+    // and every row not reached is read to its end, 185 us a level; the growth
+    // bound keeps the power law's exploding levels at pull).
     const int64_t mf = T + (int64_t)c.ent;             // entries of the frontier
     const int64_t mu = a.nnz - (int64_t)c.seen - mf;   // and of the vertices not reached
     const bool push =

@@ -7,8 +7,8 @@
 //                    columns of x as push work items
 //   k_entry_push     y = A x over the column-entry view of the listed columns
 //   k_entry_pull     y = A x by streaming the row-entry view; with the choice
-//                    open, every workgroup takes it from the masks and pushes
-//                    instead where it says so
+//                    open, every workgroup takes it from the blocker's counts
+//                    and pushes instead where it says so
 //   k_ce_*           the column-entry view from the row-entry view, at upload
 #include <algorithm>
 #include <climits>

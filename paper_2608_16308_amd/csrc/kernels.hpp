@@ -298,8 +298,8 @@ hipError_t launch_rows_batch(const DevMatrix &A, const DevCtx &C, int mode, int3
 hipError_t launch_finalize_batch(const DevMatrix &A, const DevCtx &C, int mode, int32_t nb, int32_t NB,
                                  double *yaccb, void *y, float *y32, hipStream_t s);
 // BFS over the entry views (A.re_info): the start, then one launch per level;
-// a level after the last returns at once.  policy 0 with th3 <= 0 pushes
-// while the frontier's columns hold less than push_share of the entries.
+// a level after the last returns at once.  policy 0 with th3 <= 0 pushes by
+// the rule at DBS_BFS_PUSH_ENTRIES, push_share being that share.
 hipError_t launch_bfs_start(const DevMatrix &A, const DevBfs &B, int32_t source, int32_t *level, int32_t *parent,
                             hipStream_t s);
 hipError_t launch_bfs_level(const DevMatrix &A, const DevBfs &B, int32_t l, int32_t *level, int32_t *parent,
