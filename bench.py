@@ -6,13 +6,15 @@ Workload (one "step"): y = A x on a power-law R-MAT scale-20 matrix
 U(0,1) values; 1,048,576 x 1,048,576, ~31.4M nonzeros) for eight sparse x:
 densities 0.01%, 0.1%, 1%, 10%, each with uniform indices and with indices
 clustered in 64-aligned runs of 64 (values U(0,1)); plus-times, automatic
-push/pull choice.  Every call runs the whole path: vector blocker, active
-block scan + path choice, push or pull traversal with block microkernels and
-LDS writeback, and compaction of the sparse y.  Inputs are resident in HBM
+push/pull choice.  Every call runs the whole path: vector blocker, path
+choice, push or pull traversal (the matrix is one of short COO blocks, so over
+its entry views), and compaction of the sparse y.  Inputs are resident in HBM
 when timing starts.
 
-`value` is GB/s of algorithmic bytes (paper_2608_16308_amd.bytes_model) over
-the timed steps.  Also reported: per-density GB/s and GFLOP/s (useful flops
+`value` is GB/s of algorithmic bytes (paper_2608_16308_amd.bytes_model: what the
+calls have to move over the data they run on, here the entry views) over the
+timed steps; block_traversal_model holds the same calls in the bytes of a
+traversal of the 16x16 blocks.  Also reported: per-density GB/s and GFLOP/s (useful flops
 2 * sum of nnz of the active columns, and the paper's SpMV convention
 2 * nnz(A)); the roofline of the traversal kernels from HIP events on the
 library's stream, quoted from the cold protocol (every call alone after a
@@ -47,7 +49,8 @@ def log(*a):
 def kernel_sources_digest() -> str:
     import hashlib
     h = hashlib.sha256()
-    for f in ("kernels.hip", "entries.hip", "bfs.hip", "decode.hip", "device_common.hpp", "db_format.hpp", "kernels.hpp"):
+    for f in ("kernels.hip", "entries.hip", "bfs.hip", "decode.hip", "device_common.hpp", "db_format.hpp", "kernels.hpp",
+              "turn_queue.hpp"):
         with open(os.path.join(ROOT, "paper_2608_16308_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -166,7 +169,7 @@ def other_configs(args, torch, dbs, wl, dev, flush):
         dxi, dxv = torch.from_numpy(xi).to(dev), torch.from_numpy(xv).to(dev)
         call = lambda: ctx.spmspv_raw(A, dxi, dxv, y_idx, y_val, y_nnz)
         st = ctx.spmspv_raw(A, dxi, dxv, y_idx, y_val, y_nnz, stats=True)
-        mod = model.call(xi, st["path"])
+        mod = model.call(xi, st["path"], asked="auto")
         us = _time_call(torch, call, reps)
         cold, _, cold_trav, _ = _cold_us(torch, call, reps, flush, ctx)
         rows.append({"density": d, "k": int(xi.size), "path": st["path"], "n_nzblk": st["n_nzblk"],
@@ -400,18 +403,33 @@ def run_ablation(args, torch, dbs, wl, dev):
         del ctx, A
     out["fem_formats"] = {"matrix": f"fem 56^3 x 3 dof, n={f.n}, nnz={f.nnz}", "results": fem}
 
-    # (2c) storage (Table 4 analog): DB vs CSR vs CSR+CSC for every config
+    # (2c) storage (Table 4 analog): DB vs CSR vs CSR+CSC for every config; beside
+    # it what the device matrix carries besides the format (entry views, block list)
+    def carried(mtx, hm):
+        V = mtx.vals.dtype.itemsize
+        d = hm.arrays()["desc"]
+        nnz_b = ((d >> np.uint64(8)) & np.uint64(0xFF)).astype(np.int64) + 1
+        extra = 0
+        if 2 * int(nnz_b[(d & np.uint64(7)) == 0].sum()) >= mtx.nnz:
+            rows = int((np.diff(mtx.row_ptr) > 0).sum())
+            extra += mtx.nnz * (8 + 2 * V) + 4 * (mtx.n + 1) + 4 * rows + (8 * (mtx.m + 1) if mtx.m == mtx.n else 0)
+        if mtx.nnz >= 8 * d.size:
+            extra += 12 * d.size + 16 * ((mtx.m + 15) // 16)
+        return extra
+
     store = []
     for name, mk in (("tiny", lambda: wl.tiny()), ("rmat20", lambda: a), ("mesh126", lambda: wl.mesh()),
                      ("fem56x3", lambda: f), ("decode_11008x4096", lambda: wl.decode_layer(11008, 4096)),
                      ("decode_4096x14336", lambda: wl.decode_layer(4096, 14336))):
         mtx = mk()
-        info = dbs.HostMatrix.from_csr(mtx.m, mtx.n, mtx.row_ptr, mtx.col_idx, mtx.vals).info()
+        hm = dbs.HostMatrix.from_csr(mtx.m, mtx.n, mtx.row_ptr, mtx.col_idx, mtx.vals)
+        info = hm.info()
         store.append({"config": name, "n": mtx.n, "nnz": mtx.nnz, "nblk": info["nblk"],
                       "blocks_by_type": info["blocks_by_type"],
                       "db_MiB": round(info["db_bytes"] / 2**20, 2), "csr_MiB": round(info["csr_bytes"] / 2**20, 2),
                       "csr_csc_MiB": round(info["csr_csc_bytes"] / 2**20, 2),
-                      "saving_vs_csr_csc": round(1 - info["db_bytes"] / info["csr_csc_bytes"], 4)})
+                      "saving_vs_csr_csc": round(1 - info["db_bytes"] / info["csr_csc_bytes"], 4),
+                      "device_carries_besides_MiB": round(carried(mtx, hm) / 2**20, 2)})
         log(f"[ablation] storage {store[-1]}")
     out["storage"] = store
 
@@ -580,9 +598,11 @@ def main():
     for p in points:
         st = ctx.spmspv_raw(A, p["d_idx"], p["d_val"], y_idx, y_val, y_nnz, stats=True)
         p["path"] = st["path"]
-        p["model"] = model.call(p["x_idx"], st["path"])
+        p["model"] = model.call(p["x_idx"], st["path"], asked="auto")
+        p["blocks"] = model.call(p["x_idx"], st["path"], blocks=True)
         assert p["model"]["n_nzblk"] == st["n_nzblk"] and p["model"]["y_nnz"] == st["y_nnz"]
     step_bytes = sum(p["model"]["bytes_total"] for p in points)
+    step_block_bytes = sum(p["blocks"]["bytes_total"] for p in points)
     step_main_bytes = sum(p["model"]["bytes_main"] for p in points)
     if args.profile_run == "cold":
         profile_cold(args, torch, dbs, wl, dev, ctx, A, points, run)
@@ -719,7 +739,8 @@ def main():
         # call (HIP events on the library stream)
         "roofline": {"bound": "hbm", "achieved": round(cold_achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(cold_achieved / HBM_PEAK_GBS, 4), "traffic": read_traffic(kernel_sources_digest()),
-                     "kernel": "k_traverse (push/pull traversal)", "protocol": "cold",
+                     "kernel": "k_entry_pull / k_entry_push (entry views)" if points[0]["model"]["views"]
+                     else "k_traverse (push/pull traversal)", "protocol": "cold",
                      "avg_launch_us": round(cold_main_s / len(points) * 1e6, 2),
                      "algorithmic_bytes_per_launch": round(step_main_bytes / len(points)),
                      "frac_median_times": round(step_main_bytes / cold_median_main_s / 1e9 / HBM_PEAK_GBS, 4),
@@ -735,6 +756,9 @@ def main():
         "compulsory": {"bytes_per_step": int(step_comp),
                        "GBs": round(step_comp * args.steps / elapsed / 1e9, 2),
                        "model_over_compulsory": round(step_bytes / step_comp, 3)},
+        # the same calls in the bytes that a traversal of the blocks would move
+        "block_traversal_model": {"bytes_per_step": int(step_block_bytes),
+                                  "GBs": round(step_block_bytes * args.steps / elapsed / 1e9, 2)},
         "cpu_baseline": {"value": round(cpu_value, 4), "unit": "GB/s", "cores": 1, "kind": "oracle",
                          "sample": f"{reps} passes over the same 8 x vectors on R-MAT {args.scale} "
                                    f"({cpu_s:.1f} s, CSC built once outside the timing); GB/s counts the "
@@ -778,8 +802,8 @@ def main():
         hm_gteps = len(gteps) / sum(1.0 / x for x in gteps)
         log(f"[bench] BFS: harmonic mean {hm_gteps:.2f} GTEPS over {len(srcs)} sources; {per_src[:3]}")
         result["bfs"] = {"workload": f"rmat{args.bfs_scale}_bfs_{len(srcs)}_sources", "gteps_hmean": round(hm_gteps, 3),
-                         "selector": "per level push iff the frontier's columns hold < 2% of the entries, or < 10%, "
-                                     "fewer than the unreached vertices' and < 4 times the level before",
+                         "selector": "per level push iff the frontier is listed and its columns hold < 2% of the entries, or "
+                                     "< 10%, fewer than the unreached vertices' and < 4 times the level before",
                          "gteps_min": round(min(gteps), 3), "gteps_max": round(max(gteps), 3),
                          "ms_mean": round(1e3 * float(np.mean(times)), 3), "db_build_s": round(gbuild, 2),
                          "edges_counted": "undirected edges of the source's component", "per_source": per_src}

@@ -1,10 +1,28 @@
-"""Algorithmic bytes of one SpMSpV call on the DB format (measurement only).
+"""Algorithmic bytes of one SpMSpV call (measurement only).
 
 Replays, on the host and from the same inputs, the decisions the kernels
-take -- the global path (s_b = N_nzblk / N_blk < th3, Sec. 3.3.1), which
-blocks are visited, the microkernel of each visited block (format x vector
-block mask, Sec. 3.3.3) -- and counts the bytes each step must move, every
-distinct element once per kernel that needs it:
+take -- the global path (s_b = N_nzblk / N_blk < th3, Sec. 3.3.1), whether
+the call runs over the entry views or over the blocks, which blocks are
+visited, the microkernel of each visited block (format x vector block mask,
+Sec. 3.3.3) -- and counts the bytes each step must move, every distinct
+element once per kernel that needs it.
+
+Over the entry views (at least half of the entries in COO blocks, no forced
+block format; pull, or at most as many x indices as vector blocks), E being
+the stored entries of the listed columns:
+
+  blocker   k indices + k values read, k values written to the dense x, 4 B
+            mask word update per index; where push is not ruled out on the
+            host also 8 B of column pointers per index and a 16 B work item
+            written per listed column with entries
+  push      16 B per work item; 4 B row + V per entry of E
+  pull      4 B column word per stored entry of the matrix + 4 B per chunk of
+            256; the mask words (2 B per vector block); V per entry of E, V
+            per x entry, 4 B row per row of y
+  both      8 B accumulator per row of y, 4 B per word of the y structure
+  finalize  as below
+
+Over the blocks:
 
   blocker   k indices + k values read, k values written to the dense x,
             4 B mask word update per index
@@ -42,7 +60,7 @@ _POPC16 = np.array([bin(i).count("1") for i in range(1 << 16)], dtype=np.int32)
 
 
 class BytesModel:
-    def __init__(self, m, n, row_ptr, col_idx, arrays: dict, info: dict, vbytes: int):
+    def __init__(self, m, n, row_ptr, col_idx, arrays: dict, info: dict, vbytes: int, forced: bool = False):
         self.m, self.n, self.V = int(m), int(n), int(vbytes)
         self.nblk, self.nseg = int(info["nblk"]), int(info["nseg"])
         self.nbr, self.nbc = int(info["nbr"]), int(info["nbc"])
@@ -70,8 +88,22 @@ class BytesModel:
         self.er_local = (er & 15).astype(np.int64)
         self.ec = ec
         self.col_nnz = np.bincount(ec, minlength=self.n)
+        # (the entry-view rule of the builder; a forced format is given by the caller)
+        self.entries = not forced and 2 * int(self.bnnz[self.btype == COO].sum()) >= self.nnz
 
-    def call(self, x_idx, path: str, th3: float = 0.01) -> dict:
+    def _items(self, k: int, path: str, th3: float) -> bool:
+        """Whether the blocker lists push items (path: as asked for)."""
+        if path != "auto":
+            return path == "push"
+        lim, lim_s, nlo = th3 * self.nbc, 0.12 * self.nbc, (k + 15) // 16
+        known_pull = k >= lim and (nlo >= max(lim, lim_s) or (nlo >= lim and k >= 2 * lim_s))
+        return not known_pull
+
+    def call(self, x_idx, path: str, th3: float = 0.01, asked: str | None = None, blocks: bool = False) -> dict:
+        """path: the path taken ("auto": by the paper's rule); asked: the path
+        the caller asked for (default: the same); blocks: count the traversal
+        of the blocks also where the call runs over the entry views."""
+        asked = path if asked is None else asked
         V = self.V
         x_idx = np.asarray(x_idx, dtype=np.int64)
         k = int(x_idx.size)
@@ -124,9 +156,22 @@ class BytesModel:
                 + 8 * seg_rows + 4 * segs_hit
         main += V * k
         finalize = 2 * self.nbr + y_nnz * (8 + 8 + 4 + V) + 4 * N
+        views = self.entries and not blocks and (path == "pull" or k <= self.nbc)
+        if views:
+            items = self._items(k, asked, th3) and k <= self.nbc
+            listed = int((self.col_nnz[x_idx] > 0).sum()) if items else 0
+            scan = 0
+            if items:
+                blocker += 8 * k + 16 * listed
+            yrow = np.unique(self.brow[eb_m] * 16 + self.er_local[em])
+            main = 8 * y_nnz + 4 * int(np.unique(yrow >> 5).size)
+            if path == "push":
+                main += 16 * listed + useful * (4 + V)
+            else:
+                main += 4 * self.nnz + 4 * ((self.nnz + 255) // 256) + 2 * self.nbc + useful * V + V * k + 4 * y_nnz
         total = blocker + scan + main + finalize
         compulsory = useful * (V + 1) + 8 * k + (4 + V) * y_nnz
-        return {"path": path, "k": k, "n_nzblk": N, "visited_blocks": nact_blocks,
+        return {"path": path, "views": views, "k": k, "n_nzblk": N, "visited_blocks": nact_blocks,
                 "useful_nnz": useful, "y_nnz": y_nnz, "bytes_blocker": blocker, "bytes_scan": scan,
                 "bytes_main": int(main), "bytes_finalize": finalize, "bytes_total": int(total),
                 "bytes_compulsory": int(compulsory)}
@@ -140,7 +185,7 @@ class BytesModel:
         (When pull is known on the host, the scan-free pass writes no dense
         x or masks and runs no scan: it moves about 2 V n + 2 nbc bytes
         fewer than charged here, under 0.1% of a decode layer's bytes.)"""
-        r = self.call(x_idx, path, th3)
+        r = self.call(x_idx, path, th3, blocks=True)
         V, m, n = self.V, self.m, self.n
         r["bytes_blocker"] = 2 * V * n + n // 8
         r["bytes_finalize"] = m * (8 + 8 + V) + m // 8 + n // 8 + V * n
