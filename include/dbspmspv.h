@@ -414,12 +414,12 @@ dbs_status dbs_spmspv_dense(dbs_ctx *ctx, const dbs_matrix *A, const void *d_x_d
  * stats counts the union of the vectors' vector blocks).  On a matrix without
  * COO blocks some calls share a pass with a lane per row instead: those with
  * fewer than eight entries per block, and with 256 block rows and more two
- * fp32 vectors or, where block rows hold less than two blocks, up to four fp32
- * or two fp16 vectors.  Otherwise (COO blocks and fewer than eight entries per
- * block), or for nb = 1, the vectors are taken one dbs_spmspv_dense call each.
- * A call that needs them (statistics, the lane-per-row pass, block rows taken
- * in parts)
- * allocates, once, DBS_MAX_BATCH padded x copies and fp64 accumulator sets
+ * fp32 vectors on 65536 blocks and more of at most 136 entries on average or,
+ * where block rows hold less than two blocks, up to four fp32 or two fp16
+ * vectors.  Otherwise (COO blocks and fewer than eight entries per block), or
+ * for nb = 1, the vectors are taken one dbs_spmspv_dense call each.  A call
+ * that needs them (statistics, the lane-per-row pass, block rows taken in
+ * parts) allocates, once, DBS_MAX_BATCH padded x copies and accumulator sets
  * for the context's largest shape (kept until dbs_ctx_destroy).             */
 #define DBS_MAX_BATCH 8
 dbs_status dbs_spmm_dense(dbs_ctx *ctx, const dbs_matrix *A, int32_t nb, const void *d_x, void *d_y,

@@ -881,11 +881,18 @@ extern "C" dbs_status dbs_spmm_dense(dbs_ctx *ctx, const dbs_matrix *A, int32_t 
     const int mode = A->d.dtype == DBS_F16 ? M_F16 : M_F32;
     const size_t vb = A->d.dtype == DBS_F16 ? 2 : 4;
     // the matrix-core pass, but on a matrix without COO blocks the shared pass
-    // below for two fp32 vectors (11008 x 4096: 43 against 49 us) and, where
-    // block rows hold one block, for two fp16 and up to four fp32 vectors (10^6
-    // x 16: 41 against 48 and 56 against 63)
+    // below for
+    //   two fp32 vectors on many blocks of which at most half are Dense (those
+    //   the matrix cores take as they are): 70% pruned, 3-40% active, us shared
+    //   / matrix cores 11008 x 4096 30-45 / 38-46, 5008 x 7008 26-38 / 39-50,
+    //   16384 x 16384 125-223 / 175-209; but 40% pruned 36-44 / 36-38, 31-38 /
+    //   32-39, 181-251 / 199-196, and 8000 x 2048 21-25 / 16-20, 8000 x 704
+    //   16-17 / 10-11;
+    //   two fp16 and up to four fp32 vectors where block rows hold one block
+    //   (10^6 x 16: 41 / 48 and 56 / 63)
     const bool f32 = A->d.dtype == DBS_F32, one = A->d.nblk < (int64_t)A->d.nbr * 2;
-    const int32_t most = f32 ? (one ? 4 : 2) : (one ? 2 : 0);
+    const bool light = A->d.nblk >= 65536 && A->info.nnz <= A->d.nblk * 136;
+    const int32_t most = f32 ? (one ? 4 : light ? 2 : 0) : (one ? 2 : 0);
     const bool shared = A->d.nheavy == A->d.nblk && A->d.nbr >= 256 && nb <= most;
     const bool mfma = nb > 1 && rows_mfma_fits(A->d) && !shared;
     if (!mfma && (nb == 1 || A->d.nheavy < A->d.nblk || A->d.nblk == 0)) {

@@ -701,9 +701,11 @@ hipError_t launch_bfs_level(const DevMatrix &A, const DevBfs &B, int32_t l, int3
                                            ((int64_t)A.re_nnz + 8 * BL_TPB - 1) / (8 * BL_TPB));
     // Where every wave has rows to take (four per lane and turn) one workgroup
     // per compute unit: with two, more of them queue at the counters where
-    // items are reserved (R-MAT 22 165 against 180 us).  Smaller graphs take
-    // two: a stencil of 207,360 rows takes 980 us from one source and 1078
-    // from another, with one workgroup each 1010 and 1031.
+    // items are reserved (R-MAT 22 134-143 against 142-160 us by source, R-MAT
+    // 21 107-117 / 111-132, 4M random rows of 6 348-382 / 348-417, stencils of
+    // 1.1M and 2M rows within 2%).  Smaller graphs take two: a stencil of
+    // 207,360 rows takes 980 us from one source and 1078 from another, with
+    // one workgroup each 1010 and 1031.
     const bool four = A.n >= 4 * WAVE * (BL_WAVES * 256);
     const dim3 g((uint32_t)std::min<int64_t>(want, four ? 256 : 512)), b(BL_TPB);
     if (a.th3n > 0.0 && policy == 0 && l > 0) {
