@@ -459,8 +459,9 @@ def run_ablation(args, torch, dbs, wl, dev):
 def profile_cold(args, torch, dbs, wl, dev, ctx, A, points, run):
     """Cold calls for counter passes: per sweep point --point-reps calls, each
     alone after a write of a 1 GiB buffer (the bench's cold protocol); then 20
-    warm calls of the 11008x4096 decode layer; then BFS from --bfs-sources
-    sources of R-MAT --bfs-scale.  Prints the order of the work as JSON."""
+    warm calls of the 11008x4096 decode layer with one activation and 20 with
+    eight; then BFS from --bfs-sources sources of R-MAT --bfs-scale.  Prints
+    the order of the work as JSON."""
     flush = torch.empty(1 << 28, dtype=torch.float32, device=dev)
     order = []
     for p in points:
@@ -478,6 +479,12 @@ def profile_cold(args, torch, dbs, wl, dev, ctx, A, points, run):
     y = torch.empty(w.m, dtype=torch.float16, device=dev)
     for _ in range(20):
         wctx.spmspv_dense(W, x, y=y)
+    torch.cuda.synchronize()
+    X = torch.from_numpy(np.stack([wl.decode_activation(4096, key=k) for k in range(8)])
+                         .view(np.int16)).to(dev).view(torch.float16)
+    Y = torch.empty((8, w.m), dtype=torch.float16, device=dev)
+    for _ in range(20):
+        wctx.spmm_dense(W, X, Y=Y)
     torch.cuda.synchronize()
     del wctx, W
     bfs = None
