@@ -8,7 +8,8 @@ Sec. 3.3.3) -- and counts the bytes each step must move, every distinct
 element once per kernel that needs it.
 
 Over the entry views (at least half of the entries in COO blocks, no forced
-block format; pull, or at most as many x indices as vector blocks), E being
+block format; push with at most as many x indices as vector blocks, pull with
+at most two entries per block or 15M entries), E being
 the stored entries of the listed columns:
 
   blocker   k indices + k values read, k values written to the dense x, 4 B
@@ -91,13 +92,14 @@ class BytesModel:
         # (the entry-view rule of the builder; a forced format is given by the caller)
         self.entries = not forced and 2 * int(self.bnnz[self.btype == COO].sum()) >= self.nnz
 
-    def _items(self, k: int, path: str, th3: float) -> bool:
-        """Whether the blocker lists push items (path: as asked for)."""
-        if path != "auto":
-            return path == "push"
+    def _settled(self, k: int, th3: float) -> str:
+        """What k alone settles of an automatic choice: push, pull or auto."""
         lim, lim_s, nlo = th3 * self.nbc, 0.12 * self.nbc, (k + 15) // 16
-        known_pull = k >= lim and (nlo >= max(lim, lim_s) or (nlo >= lim and k >= 2 * lim_s))
-        return not known_pull
+        if k < lim:
+            return "push"
+        if nlo >= max(lim, lim_s) or (nlo >= lim and k >= 2 * lim_s):
+            return "pull"
+        return "push" if min(k, self.nbc) < lim_s and 2 * max(nlo, -int(-lim // 1)) > k else "auto"
 
     def call(self, x_idx, path: str, th3: float = 0.01, asked: str | None = None, blocks: bool = False) -> dict:
         """path: the path taken ("auto": by the paper's rule); asked: the path
@@ -156,9 +158,11 @@ class BytesModel:
                 + 8 * seg_rows + 4 * segs_hit
         main += V * k
         finalize = 2 * self.nbr + y_nnz * (8 + 8 + 4 + V) + 4 * N
-        views = self.entries and not blocks and (path == "pull" or k <= self.nbc)
+        known = self._settled(k, th3) if asked == "auto" else asked
+        stream = self.nnz <= 2 * self.nblk or self.nnz <= 15 << 20
+        items = k <= self.nbc and (known == "push" or (known == "auto" and stream))
+        views = self.entries and not blocks and (items or (stream and path == "pull"))
         if views:
-            items = self._items(k, asked, th3) and k <= self.nbc
             listed = int((self.col_nnz[x_idx] > 0).sum()) if items else 0
             scan = 0
             if items:

@@ -701,9 +701,13 @@ dbs_status spmspv_launches(const dbs_matrix *A, DevCtx &c, hipStream_t s, int mo
     // fit the item list up to one index per vector block; an automatic choice
     // of push with the default th3 has at most a quarter of that).  No scan
     // runs; only a call that asks for statistics lets one count afterwards.
+    // Large matrices of several entries per block pull over the blocks
+    // (entry_pull_pays), also where the device has to choose.
     const bool entries = A->d.re_nchunk > 0 && A->d.re_sparse;
-    const bool items = entries && launch_path != DBS_PATH_PULL && x_nnz <= A->d.nbc;
-    if (items || (entries && launch_path == DBS_PATH_PULL)) {
+    const bool stream = entries && entry_pull_pays(A->d, mode);
+    const bool items = entries && x_nnz <= A->d.nbc &&
+                       (launch_path == DBS_PATH_PUSH || (launch_path == DBS_PATH_AUTO && stream));
+    if (items || (stream && launch_path == DBS_PATH_PULL)) {
         st = run(DBS_K_SCATTER, [&] {
             return items ? launch_entry_scatter(A->d, c, mode, x_nnz, d_x_idx, d_x_val, launch_path == DBS_PATH_AUTO, s)
                          : launch_scatter(A->d, c, mode, x_nnz, d_x_idx, d_x_val, s);
@@ -732,7 +736,7 @@ dbs_status spmspv_launches(const dbs_matrix *A, DevCtx &c, hipStream_t s, int mo
             st = run(DBS_K_SCAN, [&] { return launch_scan(A->d, c, launch_path, t3, t3s, s); });
             if (st != DBS_OK) return st;
         }
-        if (entries && launch_path == DBS_PATH_AUTO) {
+        if (stream && launch_path == DBS_PATH_AUTO) {
             st = run(DBS_K_MAIN, [&] { return launch_entry_pull(A->d, c, mode, d_mask, cm, true, false, s); });
             if (st != DBS_OK) return st;
             launch_path = DBS_PATH_PUSH;  // (the push kernel, if the device chose it)

@@ -547,6 +547,26 @@ static EntryPullArgs pull_args(const DevMatrix &A, const DevCtx &C, const uint32
     return a;
 }
 
+// The stream costs 4 bytes per entry whatever x is, and a fold of the bitmap
+// lets columns next to x's through; the traversal of the blocks costs 10-20 us
+// more to launch, 4 bytes per block, and the records of active vector blocks
+// only.  With one or two entries per block the stream is faster at every size
+// (1% clustered, 10% uniform x, us blocks / stream: R-MAT 22, 128M entries, 206 /
+// 187, 958 / 517; 16M rows of 4 554 / 263, 1466 / 1306); with more of them up to
+// a number of entries, beyond which a sparse x over many-entry blocks is better
+// left to the blocks.  fp32, 6, 14 and 28 entries per block, the same x: 16M
+// entries 52 / 52, 36 / 33, 37 / 30 and 121 / 104, 80 / 63, 74 / 49; 28-32M 105 /
+// 94, 51 / 64, 42 / 48 and 201 / 234, 168 / 145, 110 / 94; 64M 176 / 179, 99 /
+// 117, 58 / 93 and 398 / 578, 300 / 378, 298 / 250.  Boolean blocks read no value
+// and pull at a cost per block: 4M entries 31 / 17, 32 / 17, 29 / 16; 7M (28 per
+// block) 41 / 26; 16M 44 / 47, 36 / 29, 35 / 27 and, nearly every x, 68 / 115,
+// 96 / 89, 92 / 79; 14M of a stencil in natural order with 1% of x in long runs
+// 42 / 54.
+bool entry_pull_pays(const DevMatrix &A, int mode)
+{
+    return A.re_nnz <= 2 * A.nblk || A.re_nnz <= ((mode == M_BOOL ? 8 : 15) << 20);
+}
+
 hipError_t launch_entry_pull(const DevMatrix &A, const DevCtx &C, int mode, const uint32_t *omask, int complement,
                              bool scanned, bool dense_out, hipStream_t s)
 {

@@ -254,6 +254,9 @@ hipError_t launch_main(const DevMatrix &A, const DevCtx &C, int mode, const void
 //                         structure is not wanted
 //   launch_entry_push     push
 //   launch_entry_auto     the choice is taken on the device
+//   entry_pull_pays       whether pull with a sparse x over the views is the
+//                         faster way
+bool entry_pull_pays(const DevMatrix &A, int mode);
 hipError_t launch_entry_scatter(const DevMatrix &A, const DevCtx &C, int mode, int32_t k, const int32_t *x_idx,
                                 const void *x_val, bool count, hipStream_t s);
 hipError_t launch_entry_pull(const DevMatrix &A, const DevCtx &C, int mode, const uint32_t *omask, int complement,

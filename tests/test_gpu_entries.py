@@ -162,3 +162,27 @@ def test_views_of_a_device_built_matrix(torch, dtype, m, n, keep):
         y64, S = np.zeros(m), np.zeros(m)
         y64[ri], S[ri] = rv, rs
         assert oracle.within_tol(y32.cpu().numpy(), y64, S, REL_TOL).all()
+
+
+def test_large_matrix_of_many_entry_blocks(torch):
+    """16M entries in COO blocks of 24: pull goes over the blocks, push over
+    the listed columns, in turn on one context."""
+    rng = wl.rng_for(wl.W_RAND, 97, 0)
+    nbr, nbc, per, fill = 1024, 4099, 680, 24
+    J = np.argsort(rng.random((nbr, nbc)), axis=1)[:, :per]
+    cell = (rng.integers(0, 256, (nbr, per, 1)) + (2 * rng.integers(0, 128, (nbr, per, 1)) + 1) * np.arange(fill)) & 255
+    n = nbc * 16
+    key = np.sort((((np.arange(nbr)[:, None, None] * 16 + cell // 16) * n) + J[:, :, None] * 16 + cell % 16).reshape(-1))
+    a = wl.csr_from_coo(nbr * 16, n, key // n, key % n, wl._nonzero_uniform(rng, -1.0, 1.0, key.size, dtype=np.float32))
+    A, om = gpu_matrix(a), oracle_matrix(a)
+    i = A.info()
+    assert i["blocks_by_type"]["coo"] == i["nblk"] and i["nnz"] > max(15 << 20, 2 * i["nblk"])
+    ctx = dbs.Context(A)
+    mw = mask_words(rng.random(a.m) < 0.5)
+    for k in (1, 30, 300, 5000, 60000):
+        xi, xv = x_of(n, k, 3)
+        for sr in ("plus_times", "or_and"):
+            for p in ("pull", "push", "auto"):
+                label = f"many-entry blocks k={k} {sr} {p}"
+                log(label)
+                check_spmspv(ctx, A, om, a, xi, xv.astype(np.float64), path=p, semiring=sr, mask=mw, complement=True, label=label)

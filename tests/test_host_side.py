@@ -1,5 +1,5 @@
 """The library's host side over a stand-in for the HIP runtime (fake_hip.py):
-launch grids, allocation failures."""
+launch grids, allocation failures, which kernels a call takes."""
 import fake_hip
 
 # entries far apart: every block is a COO block of one entry, so that the
@@ -167,3 +167,47 @@ assert spmm() == 0 and allocs.value == 2
 allocs.value = 0
 assert spmm() == 0 and allocs.value == 0
 """)
+
+
+ROUTES = MATRIX + """
+import re
+fake.fake_launched.restype = ctypes.c_char_p
+
+def kernels(call):
+    fake.fake_forget()
+    assert call() == 0, lib.dbs_last_error()
+    return re.findall("k_[a-z_]+[a-z]", fake.fake_launched().decode())
+
+# nbr block rows of per_row blocks of 28 entries
+def short_blocks(nbr, per_row, dtype=np.float32):
+    cnt = np.tile(np.where(np.arange(16) < 14, 2 * per_row, 0), nbr)
+    rp = np.concatenate([[0], np.cumsum(cnt)]).astype(np.int64)
+    ci = np.tile((np.arange(per_row)[:, None] * 16 + np.arange(2)).reshape(-1), nbr * 14).astype(np.int32)
+    return 16 * nbr, 16 * per_row, rp, ci, None if dtype is None else np.ones(ci.size, dtype)
+
+def sparse(c, k, path, semiring=0):
+    x, v = np.arange(k, dtype=np.int32), np.ones(k, np.float32)
+    return kernels(lambda: lib.dbs_spmspv(c.ctx, c.A._h, semiring, k, P(x), P(v), None, 0, path, ctypes.c_float(0), P(c.y[0]),
+                                          P(c.y[1]), P(c.y[2]), None))
+"""
+
+
+def test_pull_over_entries_or_blocks():
+    """Sparse x: pull streams the entries up to a number of them, beyond it
+    only with one or two per block; push walks the listed columns always."""
+    fake_hip.run(ROUTES + """
+AUTO, PUSH, PULL, OR_AND = 0, 1, 2, 1
+for args, sr, stream in ((short_blocks(512, 640), 0, True), (short_blocks(1024, 640), 0, False),
+                         (short_blocks(300, 640), OR_AND, True), (short_blocks(512, 640), OR_AND, False),
+                         (short_blocks(512, 640, None), OR_AND, False), (list_matrix(1 << 20, 1 << 18, 16), 0, True),
+                         (list_matrix(1 << 20, 1 << 18, 16), OR_AND, True)):
+    c = Call(*args)
+    few = c.A.n < 20000
+    # (the last: a number of indices that does not settle the path)
+    for k, path in ((50, PULL), (c.A.n // 2, AUTO), (40 if few else 2000, AUTO)):
+        got = sparse(c, k, path, sr)
+        assert ("k_entry_pull" in got) == stream and ("k_traverse" in got) == (not stream), (stream, k, path, got)
+    got = sparse(c, 50, PUSH, sr)
+    assert "k_entry_push" in got and "k_traverse" not in got, got
+    del c
+""", timeout=300)
