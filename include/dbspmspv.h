@@ -390,7 +390,8 @@ dbs_status dbs_spmspv_noalloc(const dbs_matrix *A, dbs_semiring sr, int32_t x_nn
  * With AUTO and th3 <= 0, or with pull, no selector runs where one pass over
  * the matrix is the faster way whatever x: a matrix without COO blocks (n a
  * multiple of 16, x 16-byte aligned) multiplies the blocks of active vector
- * blocks, one with most entries in COO blocks streams its entries, another
+ * blocks, one with most entries in COO blocks streams its entries (with AUTO up
+ * to 20M of them; with more the device chooses between that and push), another
  * with eight entries per block and more multiplies all blocks (up to 32 MiB
  * of them, 48 for n a multiple of 16; fp16 blocks of at most 64 entries on
  * average whatever their number; not with one or two blocks per block row).

@@ -811,6 +811,20 @@ static bool mfma_for_one(const dbs_matrix *A)
     return nblk * 48 + nnz * vb <= ((A->d.n % BS ? 32 : 48) << 20) || (vb == 2 && nnz <= nblk * (MC_RUN / 2));
 }
 
+// The densified x, its masks, the counts and the choice of a dense activation.
+static dbs_status dense_scan(dbs_ctx *ctx, const dbs_matrix *A, int mode, const void *x, int path, float th3)
+{
+    const hipStream_t s = ctx->stream;
+    const double t3 = (double)norm_th3(th3), t3s = spread_th3(th3);
+    if (scan_takes_dense(A->d, x)) {
+        LAUNCH(ctx, DBS_K_SCAN, launch_scan_dense(A->d, ctx->c, mode, x, path, t3, t3s, s));
+    } else {
+        LAUNCH(ctx, DBS_K_SCATTER, launch_ballot(A->d, ctx->c, mode, x, s));
+        LAUNCH(ctx, DBS_K_SCAN, launch_scan(A->d, ctx->c, path, t3, t3s, s));
+    }
+    return DBS_OK;
+}
+
 extern "C" dbs_status dbs_spmspv_dense(dbs_ctx *ctx, const dbs_matrix *A, const void *d_x_dense,
                                        dbs_path path, float th3, void *d_y_dense, float *d_y_f32,
                                        dbs_call_stats *stats)
@@ -832,11 +846,22 @@ extern "C" dbs_status dbs_spmspv_dense(dbs_ctx *ctx, const dbs_matrix *A, const 
         // itself, without a scan, and writes y itself
         LAUNCH(ctx, DBS_K_MAIN, launch_rows_dx(A->d, ctx->c, mode, d_x_dense, d_y_dense, d_y_f32, s));
     } else if (A->d.re_sparse && path != DBS_PATH_PUSH && !(path == DBS_PATH_AUTO && th3 > 0.f)) {
-        // short COO blocks: the row-entry view, whatever the selector would
-        // choose (the scan only counts and chooses for the statistics)
-        LAUNCH(ctx, DBS_K_SCATTER, launch_ballot(A->d, ctx->c, mode, d_x_dense, s));
-        LAUNCH(ctx, DBS_K_MAIN, launch_entry_pull(A->d, ctx->c, mode, nullptr, 0, false, true, s));
-        if (stats)
+        // short COO blocks: the row-entry view.  A stream of up to 20M entries
+        // is the faster way whatever x (the scan only counts and chooses for
+        // the statistics); with more the scan runs first and few active
+        // vector blocks push over the blocks: 32768 x 16384 6% kept, fp32, 0.05
+        // / 3 / 10% active 31 / 55 / 57 us streamed, 24 / 58 / 118 with the
+        // blocks; 49152 x 49152 3% kept, fp16, 57 / 86 / 106, 26 / 127 / 254.
+        const bool choose = path == DBS_PATH_AUTO && A->d.re_nnz > 20 << 20;
+        if (choose) {
+            if ((st = dense_scan(ctx, A, mode, d_x_dense, p, th3)) != DBS_OK) return st;
+        } else {
+            LAUNCH(ctx, DBS_K_SCATTER, launch_ballot(A->d, ctx->c, mode, d_x_dense, s));
+        }
+        LAUNCH(ctx, DBS_K_MAIN, launch_entry_pull(A->d, ctx->c, mode, nullptr, 0, choose, true, s));
+        if (choose)
+            LAUNCH(ctx, DBS_K_MAIN, launch_main(A->d, ctx->c, mode, ctx->c.xd, nullptr, 0, nullptr, DBS_PATH_PUSH, s));
+        else if (stats)
             LAUNCH(ctx, DBS_K_SCAN, launch_scan(A->d, ctx->c, p, (double)norm_th3(th3), spread_th3(th3), s));
         LAUNCH(ctx, DBS_K_FINALIZE, launch_finalize_dense(A->d, ctx->c, mode, d_y_dense, d_y_f32, s));
     } else if (mfma_for_one(A) && path != DBS_PATH_PUSH && !(path == DBS_PATH_AUTO && th3 > 0.f)) {
@@ -850,13 +875,7 @@ extern "C" dbs_status dbs_spmspv_dense(dbs_ctx *ctx, const dbs_matrix *A, const 
             LAUNCH(ctx, DBS_K_FINALIZE, launch_finalize_dense(A->d, ctx->c, mode, nullptr, nullptr, s));
         }
     } else {
-        if (scan_takes_dense(A->d, d_x_dense)) {
-            LAUNCH(ctx, DBS_K_SCAN,
-                   launch_scan_dense(A->d, ctx->c, mode, d_x_dense, p, (double)norm_th3(th3), spread_th3(th3), s));
-        } else {
-            LAUNCH(ctx, DBS_K_SCATTER, launch_ballot(A->d, ctx->c, mode, d_x_dense, s));
-            LAUNCH(ctx, DBS_K_SCAN, launch_scan(A->d, ctx->c, p, (double)norm_th3(th3), spread_th3(th3), s));
-        }
+        if ((st = dense_scan(ctx, A, mode, d_x_dense, p, th3)) != DBS_OK) return st;
         LAUNCH(ctx, DBS_K_MAIN, launch_main(A->d, ctx->c, mode, ctx->c.xd, nullptr, 0, nullptr, p, s));
         LAUNCH(ctx, DBS_K_FINALIZE, launch_finalize_dense(A->d, ctx->c, mode, d_y_dense, d_y_f32, s));
     }

@@ -186,3 +186,34 @@ def test_large_matrix_of_many_entry_blocks(torch):
                 label = f"many-entry blocks k={k} {sr} {p}"
                 log(label)
                 check_spmspv(ctx, A, om, a, xi, xv.astype(np.float64), path=p, semiring=sr, mask=mw, complement=True, label=label)
+
+
+@pytest.mark.parametrize("dtype,m,n", [(np.float32, 12003, 30017), (np.float16, 12000, 30016)])
+def test_dense_activation_on_many_entries(torch, dtype, m, n):
+    """More than 20M entries in short COO blocks: the scan chooses between the
+    stream and push; nearly empty activations (push) and others in turn."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+    dt = torch.float32 if dtype == np.float32 else torch.float16
+    w = torch.where(torch.rand((m, n), device="cuda", generator=g) < 0.065,
+                    torch.rand((m, n), device="cuda", generator=g) - 0.5, torch.zeros((), device="cuda")).to(dt)
+    A = dbs.Matrix.from_dense(w)
+    i = A.info()
+    assert i["nnz"] > 20 << 20 and i["nnz"] < 32 * i["nblk"]
+    ctx = dbs.Context(A)
+    w64 = w.double()
+    taken = set()
+    for active in (0.0003, 0.2, 0.02, 0.0003, 0.0, 1.0):
+        x = (torch.randn(n, device="cuda", generator=g) * (torch.rand(n, device="cuda", generator=g) < active)).to(dt)
+        ref, S = w64 @ x.double(), w64.abs() @ x.double().abs()
+        for path in ("auto", "pull"):
+            log(f"dense on many entries {dtype.__name__} {m}x{n} active={active} {path}")
+            for stats in (False, True):
+                y32 = torch.full((m,), -7.0, device="cuda")
+                out = ctx.spmspv_dense(A, x, y32=y32, path=path, stats=stats)
+                torch.cuda.synchronize()
+                y = out[0] if stats else out
+                if stats and path == "auto":
+                    taken.add(out[1]["path"])
+                assert bool(((y32.double() - ref).abs() <= REL_TOL * S).all())
+                assert torch.equal(y, y32) if dtype == np.float32 else bool(((y.double() - ref).abs() <= 2.0 ** -10 * ref.abs() + 2.0 ** -24).all())
+    assert taken == {"push", "pull"}

@@ -211,3 +211,18 @@ for args, sr, stream in ((short_blocks(512, 640), 0, True), (short_blocks(1024, 
     assert "k_entry_push" in got and "k_traverse" not in got, got
     del c
 """, timeout=300)
+
+
+def test_dense_activation_over_entries():
+    """Short COO blocks: the stream alone up to 20M entries and for pull, beyond
+    with the scan and the push kernel."""
+    fake_hip.run(ROUTES + """
+AUTO, PUSH, PULL = 0, 1, 2
+for args, path, choose in ((short_blocks(512, 640), AUTO, False), (short_blocks(1200, 640), AUTO, True),
+                           (short_blocks(1200, 640), PULL, False)):
+    c = Call(*args)
+    x, y = np.ones(c.A.n, np.float32), np.zeros(c.A.m, np.float32)
+    got = kernels(lambda: lib.dbs_spmspv_dense(c.ctx, c.A._h, P(x), path, ctypes.c_float(0), P(y), None, None))
+    assert "k_entry_pull" in got and ("k_scan" in got) == ("k_traverse" in got) == choose, (path, choose, got)
+    del c
+""", timeout=300)
