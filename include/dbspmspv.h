@@ -393,8 +393,8 @@ dbs_status dbs_spmspv_noalloc(const dbs_matrix *A, dbs_semiring sr, int32_t x_nn
  * blocks, one with most entries in COO blocks streams its entries (with AUTO up
  * to 20M of them; with more the device chooses between that and push), another
  * with eight entries per block and more multiplies all blocks (up to 32 MiB
- * of them, 48 for n a multiple of 16; fp16 blocks of at most 64 entries on
- * average whatever their number; not with one or two blocks per block row).
+ * of them, 48 for n a multiple of 16; not with one or two blocks per block
+ * row).
  * stats then reports what the selector would have counted and chosen.  All
  * other calls, and th3 > 0, let the device choose as in dbs_spmspv (but a
  * matrix without COO blocks takes pull, see DBS_TH3_DEFAULT).

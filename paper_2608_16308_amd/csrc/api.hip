@@ -798,17 +798,18 @@ extern "C" dbs_status dbs_spmspv(dbs_ctx *ctx, const dbs_matrix *A, dbs_semiring
 //   7999 x 7999   70% pruned   fp16 (48 MiB) 24-44 / 40-44, fp32 (85 MiB) 26-47 / 42-60
 //   8000 x 8000   80% pruned   fp16 (36 MiB) 34-54 / 26-32, fp32 (60 MiB) 36-57 / 36-59
 //   4500 x 4000   half pruned  fp32 (38 MiB) 28-42 / 20-31
-//   16384 x 16384 80% pruned   fp16 (150 MiB) 75-150 / 90-95, fp32 (252 MiB) 84-187 / 146-210
+//   16384 x 16384 80% pruned   fp16 (150 MiB) 61-146 / 88-106, fp32 (252 MiB) 84-187 / 146-210
 // -- up to 32 MiB, 48 with whole vector blocks (x is then loaded aligned and
-// without a test), and in fp16 where a block's values fit half a run.  Block
-// rows of one or two blocks keep too few of a wave's loads in flight (10^6 x
-// 16 fp16 41 / 48, fp32 41 / 64; 500000 x 32 fp16 32 / 28, fp32 33 / 38).
+// without a test); an activation of 0.05% then takes up to 5 us more (5003 x
+// 7001 87% pruned fp32 25 / 30).  Block rows of one or two blocks keep too few
+// of a wave's loads in flight (10^6 x 16 fp16 41 / 48, fp32 41 / 64; 500000 x 32
+// fp16 32 / 28, fp32 33 / 38).
 static bool mfma_for_one(const dbs_matrix *A)
 {
     if (!rows_mfma_fits(A->d)) return false;
     const int64_t nblk = A->d.nblk, nnz = A->info.nnz, vb = dtype_bytes((dbs_dtype)A->d.dtype);
     if (nblk < (int64_t)A->d.nbr * (vb == 2 ? 2 : 3)) return false;
-    return nblk * 48 + nnz * vb <= ((A->d.n % BS ? 32 : 48) << 20) || (vb == 2 && nnz <= nblk * (MC_RUN / 2));
+    return nblk * 48 + nnz * vb <= (A->d.n % BS ? 32 : 48) << 20;
 }
 
 // The densified x, its masks, the counts and the choice of a dense activation.

@@ -226,3 +226,28 @@ for args, path, choose in ((short_blocks(512, 640), AUTO, False), (short_blocks(
     assert "k_entry_pull" in got and ("k_scan" in got) == ("k_traverse" in got) == choose, (path, choose, got)
     del c
 """, timeout=300)
+
+
+def test_dense_activation_on_filled_blocks():
+    """All blocks at once up to 32 MiB of them, 48 MiB with whole vector blocks,
+    in either type; beyond the device chooses."""
+    fake_hip.run(ROUTES + """
+# blocks of 44 entries, the first one a COO block of 11; cut: the last vector block has 12 columns
+def filled(nbr, nbc, dtype, cut):
+    cols = np.add.outer(np.arange(nbc) * 16, np.arange(11)).reshape(-1).astype(np.int32)
+    ci = np.concatenate([cols] + [cols[11:]] * 3 + [cols] * (4 * nbr - 4))
+    cnt = np.tile(np.where(np.arange(16) < 4, cols.size, 0), nbr)
+    cnt[1:4] -= 11
+    return 16 * nbr, 16 * nbc - (4 if cut else 0), np.concatenate([[0], np.cumsum(cnt)]).astype(np.int64), ci, np.ones(ci.size, dtype)
+
+for dtype, nbr, cut, cores in ((np.float32, 480, False, True), (np.float32, 480, True, False), (np.float32, 600, False, False),
+                               (np.float16, 800, False, True), (np.float16, 1000, False, False), (np.float16, 400, True, True)):
+    c = Call(*filled(nbr, 450, dtype, cut))
+    assert c.A.info()["blocks_by_type"]["coo"] == 1
+    mib = (c.A.info()["nblk"] * 48 + c.A.info()["nnz"] * np.dtype(dtype).itemsize) / 2.0 ** 20
+    assert (mib < (32 if cut else 48)) == cores, mib
+    x, y = np.ones(c.A.n, dtype), np.zeros(c.A.m, dtype)
+    got = kernels(lambda: lib.dbs_spmspv_dense(c.ctx, c.A._h, P(x), 0, ctypes.c_float(0), P(y), None, None))
+    assert ("k_rows_mfma" in got) == cores and ("k_scan" in got) == (not cores), (dtype, nbr, cut, got)
+    del c
+""", timeout=300)
