@@ -37,6 +37,13 @@ constexpr int BL_PUSH_QUEUE = 4096;  // found vertices queued in LDS before thei
 constexpr int BL_PULL_QUEUE = 1024;  // pull: with more per workgroup the next level pulls again
 constexpr int BL_ROWS = 256;         // rows per wave and turn of pull, at most
 constexpr int BL_LANE = 8;           // entries a lane looks at alone
+// Rows with more than BL_LONG entries left after a wave's first two rounds
+// (584 entries) are read by the whole workgroup, up to BL_LONG_ROWS of them: a
+// row of 2^20 entries without a parent in the frontier took its wave 9 ms a
+// level (a BFS that meets four of them in three levels 110 ms, with the
+// workgroup 4.3; R-MAT and stencils, which have few such rows, within 1%).
+constexpr int32_t BL_LONG = 8192;
+constexpr int BL_LONG_ROWS = 32;
 
 struct BfsArgs {
     const int2 *rowinfo;
@@ -71,11 +78,14 @@ struct BfsLds {
             int32_t beg[BL_WAVES][BL_ROWS], end[BL_WAVES][BL_ROWS];
             uint32_t out[BL_WAVES][BL_ROWS / 32];  // rows found
             uint32_t hit[BL_WAVES][WAVE];          // column found for a lane's row
+            // long rows: id, next entry, end, entries for the count of those found
+            int32_t lv[BL_LONG_ROWS], lp[BL_LONG_ROWS], le[BL_LONG_ROWS], ln[BL_LONG_ROWS];
         } pull;
     };
     uint64_t tot[BL_WAVES];
     uint64_t base, ent;
     uint32_t nq, found, inc, nvb;
+    uint32_t nlong, lhit;
 };
 
 // The push queue of a workgroup (queue_is_full).
@@ -183,7 +193,8 @@ __global__ __launch_bounds__(BL_TPB, 8) void k_bfs_level(BfsArgs a, int32_t l)
     int4 *const nitems = a.items[(l + 1) & 1];
     const bool nvb = a.th3n > 0.0;
     if (t == 0) {
-        L.nq = L.found = L.inc = L.nvb = 0;
+        L.nq = L.found = L.inc = L.nvb = L.nlong = 0;
+        L.lhit = 0xFFFFFFFFu;
         L.ent = 0;
     }
     __syncthreads();
@@ -390,6 +401,16 @@ __global__ __launch_bounds__(BL_TPB, 8) void k_bfs_level(BfsArgs a, int32_t l)
                     p += take;
                     if (open) hit = got;
                     open = open && got == 0xFFFFFFFFu && p < end;
+                    if (most > WAVE && open && end - p > BL_LONG) {
+                        const uint32_t at = atomicAdd(&L.nlong, 1u);
+                        if (at < BL_LONG_ROWS) {
+                            L.pull.lv[at] = v0 + r;
+                            L.pull.lp[at] = p;
+                            L.pull.le[at] = end;
+                            L.pull.ln[at] = end - beg;
+                            open = false;
+                        }
+                    }
                 }
                 const bool h = hit != 0xFFFFFFFFu;
                 if (h) {
@@ -433,6 +454,46 @@ __global__ __launch_bounds__(BL_TPB, 8) void k_bfs_level(BfsArgs a, int32_t l)
         ents = wave_sum(ents);
         if (lane == 0 && ents) atomicAdd((unsigned long long *)&L.ent, (unsigned long long)ents);
         __syncthreads();
+        const uint32_t nlong = min(L.nlong, (uint32_t)BL_LONG_ROWS);  // (nothing is added after the barrier)
+        if (nlong) {
+            // (the words of the next bitmap that other waves stored are in memory)
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+        }
+        for (uint32_t i = 0; i < nlong; ++i) {
+            const int32_t end = L.pull.le[i];
+            uint32_t got = 0xFFFFFFFFu;
+            for (int64_t p = L.pull.lp[i]; p < end && got == 0xFFFFFFFFu; p += BL_LANE * BL_TPB) {
+                const int32_t left = end - (int32_t)p;
+                uint32_t cw[BL_LANE], f[BL_LANE], hit = 0xFFFFFFFFu;
+#pragma unroll
+                for (int k = 0; k < BL_LANE; ++k) cw[k] = k * BL_TPB + t < left ? a.col[p + k * BL_TPB + t] & ~RE_START : 0u;
+#pragma unroll
+                for (int k = 0; k < BL_LANE; ++k) f[k] = k * BL_TPB + t < left ? F[cw[k] >> 5] : 0u;
+#pragma unroll
+                for (int k = BL_LANE - 1; k >= 0; --k)
+                    if ((f[k] >> (cw[k] & 31)) & 1u) hit = cw[k];
+                if (hit != 0xFFFFFFFFu) atomicMin(&L.lhit, hit);
+                __syncthreads();
+                got = L.lhit;
+                __syncthreads();  // (no thread is at the next entries before every thread has read it)
+            }
+            if (got == 0xFFFFFFFFu) continue;
+            if (t == 0) {
+                const int32_t v = L.pull.lv[i];
+                a.parent[v] = got;
+                a.level[v] = l + 1;
+                const uint32_t old = atomicOr(&nb[v >> 5], 1u << (v & 31));
+                if (!((old >> (v & 16)) & 0xFFFFu)) ++L.nvb;
+                ++L.found;
+                L.ent += (uint64_t)L.pull.ln[i];
+                const uint32_t at = L.nq++;
+                if (at < BL_PULL_QUEUE) L.pull.q[at] = v;
+                else L.inc = 1u;
+                L.lhit = 0xFFFFFFFFu;
+            }
+            __syncthreads();
+        }
         if (L.inc) {
             if (t == 0) {
                 atomicAdd(&next->extra, L.found);

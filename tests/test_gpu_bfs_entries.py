@@ -60,6 +60,21 @@ def graphs():
         src += list(200 + rng.choice(n - 300, k - 1, replace=False)) + [n - 1]
         dst += [v] * k
     yield "last column", graph(n, src, dst, symmetric=False)
+    # 64 rows next to each other of 9,000 and more entries, a multiple of the
+    # workgroup's 8192 and one more and less among them: reached in the first
+    # or in the second step from the last vertex, or not at all; 32 of them are
+    # read by the workgroup, the others by their wave
+    n, late = 40000, 38000
+    src, dst = [np.full(n - late - 1, n - 1)], [np.arange(late, n - 1)]
+    for i in range(64):
+        k = [9000, 584 + 8193, 584 + 16384, 585 + 16384, 583 + 24576, 30000][i % 6]
+        cols = 200 + rng.choice(late - 1000, k - 1, replace=False)
+        src.append(np.append(cols, late + i if i % 3 == 0 else late - 500 + i if i % 3 == 1 else 150))
+        dst.append(np.full(k, 64 + i))
+    hit = np.repeat(np.arange(late, n - 1), 30)   # the second step: the columns before `late`
+    src.append(hit)
+    dst.append(late - 700 + rng.integers(0, 700, hit.size))
+    yield "long rows", graph(n, np.concatenate(src), np.concatenate(dst), symmetric=False)
     # directed, half of the vertices without outgoing edges
     n = 3000
     yield "dead ends", graph(n, rng.integers(0, n // 2, 9000), rng.integers(0, n, 9000), symmetric=False)
