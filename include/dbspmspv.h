@@ -415,9 +415,10 @@ dbs_status dbs_spmspv_dense(dbs_ctx *ctx, const dbs_matrix *A, const void *d_x_d
  * stats counts the union of the vectors' vector blocks).  On a matrix without
  * COO blocks some calls share a pass with a lane per row instead: those with
  * fewer than eight entries per block, and with 256 block rows and more two
- * fp32 vectors on 65536 blocks and more of at most 136 entries on average or,
- * where block rows hold less than two blocks, up to four fp32 or two fp16
- * vectors.  Otherwise (COO blocks and fewer than eight entries per block), or
+ * fp32 vectors on 65536 blocks and more of at most 136 entries on average (up
+ * to four with 257 to 383 block rows, then also of more entries for n no
+ * multiple of 16) or, where block rows hold less than two blocks, up to four
+ * fp32 or two fp16 vectors.  Otherwise (COO blocks and fewer than eight entries per block), or
  * for nb = 1, the vectors are taken one dbs_spmspv_dense call each.  A call
  * that needs them (statistics, the lane-per-row pass, block rows taken in
  * parts) allocates, once, DBS_MAX_BATCH padded x copies and accumulator sets

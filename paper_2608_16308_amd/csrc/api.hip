@@ -912,11 +912,19 @@ extern "C" dbs_status dbs_spmm_dense(dbs_ctx *ctx, const dbs_matrix *A, int32_t 
     //   16384 x 16384 125-223 / 175-209; but 40% pruned 36-44 / 36-38, 31-38 /
     //   32-39, 181-251 / 199-196, and 8000 x 2048 21-25 / 16-20, 8000 x 704
     //   16-17 / 10-11;
+    //   up to four where the block rows fill the compute units once and a
+    //   little (their workgroups' second round is nearly empty), also of Dense
+    //   blocks if n is ragged: three and four vectors 5008 x 7008 70% pruned
+    //   30-46 / 37-51, 33-48 / 42-51, half pruned 32-48 / 36-45, 35-49 / 39-46;
+    //   5003 x 7001 30% pruned 33-45 / 38-48, 34-45 / 40-48; but 5008 x 7008
+    //   33-44 / 33-37, and with 500 block rows, 8000 x 8000 70% pruned, 40-75 /
+    //   40-57, 50-78 / 47-57;
     //   two fp16 and up to four fp32 vectors where block rows hold one block
     //   (10^6 x 16: 41 / 48 and 56 / 63)
     const bool f32 = A->d.dtype == DBS_F32, one = A->d.nblk < (int64_t)A->d.nbr * 2;
-    const bool light = A->d.nblk >= 65536 && A->info.nnz <= A->d.nblk * 136;
-    const int32_t most = f32 ? (one ? 4 : light ? 2 : 0) : (one ? 2 : 0);
+    const bool uneven = A->d.nbr > 256 && A->d.nbr < 384;
+    const bool light = A->d.nblk >= 65536 && (A->info.nnz <= A->d.nblk * 136 || (uneven && A->d.n % BS));
+    const int32_t most = f32 ? (one ? 4 : light ? (uneven ? 4 : 2) : 0) : (one ? 2 : 0);
     const bool shared = A->d.nheavy == A->d.nblk && A->d.nbr >= 256 && nb <= most;
     const bool mfma = nb > 1 && rows_mfma_fits(A->d) && !shared;
     if (!mfma && (nb == 1 || A->d.nheavy < A->d.nblk || A->d.nblk == 0)) {

@@ -123,12 +123,14 @@ def layer(m, n, keep, dtype, key):
     return wl.csr_from_coo(m, n, r, c, wl._nonzero_uniform(rng, -1.0, 1.0, r.size, dtype=dtype))
 
 
-@pytest.mark.parametrize("dtype,m,n,keep,nbs", [(np.float32, 4112, 4094, 0.4, (2,)), (np.float32, 4100, 16, 0.85, (2, 3, 4)),
+@pytest.mark.parametrize("dtype,m,n,keep,nbs", [(np.float32, 6144, 2816, 0.4, (2,)), (np.float32, 4112, 4094, 0.4, (2, 3, 4)),
+                                                (np.float32, 4112, 4094, 0.8, (2, 4)), (np.float32, 4100, 16, 0.85, (2, 3, 4)),
                                                 (np.float16, 4100, 16, 0.85, (2,))])
 def test_shared_lane_per_row_pass(torch, dtype, m, n, keep, nbs):
-    """No COO block, 256 block rows and more: two fp32 vectors on 65536 blocks,
-    and up to four fp32 or two fp16 ones where block rows hold one block; and
-    on either side of the rule the matrix cores, on the same context."""
+    """No COO block, 256 block rows and more: two fp32 vectors on 65536 blocks
+    (four with 257 block rows), and up to four fp32 or two fp16 ones where block
+    rows hold one block; and on either side of the rule the matrix cores, on the
+    same context."""
     a = layer(m, n, keep, dtype, n)
     A, om = gpu_matrix(a), oracle_matrix(a)
     assert A.info()["blocks_by_type"]["coo"] == 0 and A.info()["nbr"] >= 256

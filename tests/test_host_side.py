@@ -251,3 +251,23 @@ for dtype, nbr, cut, cores in ((np.float32, 480, False, True), (np.float32, 480,
     assert ("k_rows_mfma" in got) == cores and ("k_scan" in got) == (not cores), (dtype, nbr, cut, got)
     del c
 """, timeout=300)
+
+
+def test_batched_activations_on_uneven_block_rows():
+    """fp32 layers without COO blocks: two vectors share the lane-per-row pass,
+    up to four with 257 to 383 block rows (there of Dense blocks too if n is
+    ragged); others take the matrix cores."""
+    fake_hip.run(ROUTES + """
+def layer(nbr, nbc, per, cut):   # per columns of every block row's blocks, in all 16 rows
+    ci = np.tile(np.add.outer(np.arange(nbc) * 16, np.arange(per)).reshape(-1).astype(np.int32), 16 * nbr)
+    return 16 * nbr, 16 * nbc - cut, (np.arange(16 * nbr + 1) * nbc * per).astype(np.int64), ci, np.ones(ci.size, np.float32)
+
+for nbr, nbc, per, cut, most in ((256, 257, 4, 0, 2), (257, 256, 4, 0, 4), (383, 172, 4, 3, 4), (384, 172, 4, 0, 2), (257, 250, 4, 0, 0),
+                                 (257, 256, 10, 0, 0), (257, 256, 10, 3, 4)):
+    c = Call(*layer(nbr, nbc, per, cut))
+    x, y = np.ones((5, c.A.n), np.float32), np.zeros((5, c.A.m), np.float32)
+    for nb in (2, 3, 4, 5):
+        got = kernels(lambda: lib.dbs_spmm_dense(c.ctx, c.A._h, nb, P(x), P(y), None, None))
+        assert ("k_rows_mfma" in got) == (nb > most) and ("k_rows" in got) == (nb <= most), (nbr, nbc, per, cut, nb, got)
+    del c
+""", timeout=300)
