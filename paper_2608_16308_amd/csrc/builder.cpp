@@ -470,19 +470,24 @@ extern "C" dbs_status dbs_host_build_csr(int32_t m, int32_t n, int64_t nnz, cons
         for (auto &a : tcount) a.fill(0);
         std::vector<int64_t> tcoo(nt, 0);  // entries in COO blocks
         parallel_chunks(nbr, 64, [&](int t, int64_t s, int64_t e) {
+            // (counted here and added once: the threads' counters share lines)
+            std::array<int64_t, DBS_NUM_BLOCK_TYPES> count{};
+            int64_t coo = 0;
             for (int64_t R = s; R < e && !fail.failed.load(); ++R) {
                 if (!gather_block_row((int32_t)R, m, n, row_ptr, col_idx, scratch[t], fail)) return;
                 RowBlockSizes rs = walk_block_row(
                     scratch[t], o, vb,
                     [&](size_t, uint32_t bn, uint32_t type, uint64_t, int32_t) {
-                        tcount[t][type]++;
-                        if (type == T_COO) tcoo[t] += bn;
+                        count[type]++;
+                        if (type == T_COO) coo += bn;
                     },
                     [](int64_t, uint32_t) {});
                 rb_nblk[R + 1] = rs.nblk;
                 rb_bytes[R + 1] = rs.bytes;
                 rb_nseg[R + 1] = rs.nseg;
             }
+            for (size_t k = 0; k < count.size(); ++k) tcount[t][k] += count[k];
+            tcoo[t] += coo;
         });
         if (fail.failed.load()) {
             delete h;
